@@ -198,7 +198,7 @@ gpulet_status gpulet_conv2d_fwd_ex(const void *x, const void *w, const float *b,
  * c < C (x_ch_stride 0 means C).  Used when several layers that read the same
  * tensor are computed as one layer and their consumers each take a slice of the
  * result (the two reduce layers of an inception block).  Only the gathering
- * tiles 0..6 read slices; another forced tile falls back as documented at
+ * tiles (0..6, 12..14) read slices; another forced tile falls back as documented at
  * gpulet_set_conv_tile.  Results have the bits of the same layer on a dense copy
  * of the slice.  Extra error: x_ch_offset < 0 or x_ch_offset + C > x_ch_stride.
  */
@@ -368,16 +368,18 @@ gpulet_status gpulet_conv2d_timeline(const void *x, const void *w, const float *
  *      pad 1, C a multiple of 64; other shapes run tile 1 instead)
  *  12: 192x128  13: 96x128 (gathering tiles with three 32-pixel row tiles per
  *      wavefront, for layers whose 128-pixel tiles just miss a whole number of
- *      rounds on a gpu-let),
+ *      rounds on a gpu-let)
+ *  14: 32x32 (gathering tile for launches that leave most CUs idle otherwise;
+ *      channel counts that are not multiples of 8 run tile 3 instead),
  * or -1 to return to automatic selection, which picks the tile whose busiest
  * CU has the least work for the launch's shape and the stream's CU count, and
  * tile 9 wherever it applies.  All tiles but 9 give bit-identical results; tile 9
  * groups the same ascending sum differently (zero padding inside the depth),
  * so it agrees with them to rounding.  Tiles 7..11 need dense input pixels and
  * a single output: a layer that reads a channel slice or stores to two tensors
- * counts as another shape for them.  GPULET_EINVAL outside -1..13.
+ * counts as another shape for them.  GPULET_EINVAL outside -1..14.
  */
-enum { GPULET_CONV_TILES = 14 };
+enum { GPULET_CONV_TILES = 15 };
 gpulet_status gpulet_set_conv_tile(int tile);
 
 /*

@@ -30,13 +30,18 @@ struct TileChoice {
 // The gathering tiles in the order in which they are tried (on a tie the earlier one wins).
 // 192x128 and 96x128 exist for the layers whose 128-pixel tiles just miss a whole number of
 // rounds on a gpu-let (98 tiles on 96 CUs, 196 on 192): three row tiles per wavefront instead
-// of two or four change the tile count enough to save a round.
+// of two or four change the tile count enough to save a round.  32x32 is for launches whose 64x64
+// tiles leave CUs idle: such a launch waits for the ~50 B/clk at which one CU takes transfers, so
+// the rows a workgroup stages (64 instead of 128 per slice) set its time: 0.55 of a 64x64 round
+// (1x1 2048 -> 512 on 7x7 at batch 1 6.6 us in 64x64, 4.7 in 32x32; 3x3/2 512 -> 512 on 14x14 12.8 and 8.5; with
+// a second workgroup on every CU it is the slower one, 512 -> 1024 on 10x10 at batch 5 4.3 against 4.0,
+// except for filters larger than 1x1 and depths from 18 slices on, see choose_kernel).
 const TileChoice kTiles[] = {{6, 256, 128, 1.00f}, {12, 192, 128, 0.93f}, {0, 128, 128, 0.90f}, {13, 96, 128, 0.80f},
                              {2, 64, 128, 0.72f},  {1, 128, 64, 0.72f},   {3, 64, 64, 0.58f},   {5, 32, 128, 0.40f},
-                             {4, 128, 32, 0.30f}};
+                             {4, 128, 32, 0.30f},  {14, 32, 32, 0.26f}};
 constexpr int kNumTiles = static_cast<int>(sizeof(kTiles) / sizeof(kTiles[0]));
 
-bool is_gathering_tile(int id) { return (id >= 0 && id <= 6) || id == 12 || id == 13; }
+bool is_gathering_tile(int id) { return (id >= 0 && id <= 6) || (id >= 12 && id <= 14); }
 
 
 }  // namespace
@@ -102,7 +107,7 @@ hipError_t make_params(const ConvArgs &a, const LaunchCtx &ctx, ConvParams &p, b
     // up to the last channel the layer reads of the last pixel
     p.x_bytes = static_cast<unsigned>(2LL * ((1LL * a.N * a.H * a.W - 1) * p.ldx + a.C));
     p.w_bytes = static_cast<unsigned>(2LL * a.K * a.R * a.S * a.C);
-    p.tap_inner = (a.C % BK == 0 && a.R * a.S > 1) ? 1 : 0;
+    p.tap_inner = (a.C % BK == 0 && a.R * a.S < 32) ? 1 : 0;   // conv_igemm keeps a bit per tap
     p.vec_store = (a.y_ch_stride % 8 == 0 && a.y_ch_offset % 8 == 0 && reinterpret_cast<uintptr_t>(a.y) % 16 == 0 &&
                    reinterpret_cast<uintptr_t>(a.b) % 16 == 0 &&
                    (!a.residual || (a.K % 8 == 0 && reinterpret_cast<uintptr_t>(a.residual) % 16 == 0)) &&
@@ -142,10 +147,10 @@ hipError_t make_params(const ConvArgs &a, const LaunchCtx &ctx, ConvParams &p, b
 }
 
 // Which kernel runs a layer: 0..6 a gathering tile (with `split` workgroups per tile), 7 the
-// patch kernel (column block `tw`), 8 the streaming 1x1 kernel, 9 the stem kernel, 10 the
+// patch kernel (column block `tw`, tile `patch_tile`), 8 the streaming 1x1 kernel, 9 the stem kernel, 10 the
 // resident-weight kernel (column block `tw64`).
 struct Choice {
-    int best, split, tw, tw64, th11, tw11;
+    int best, split, tw, tw64, th11, tw11, patch_tile;
     double cost;   // of `best` in the cost model's units when it is a gathering tile or the tall tile, else 0
 };
 
@@ -191,6 +196,9 @@ Choice choose_kernel(const ConvParams &p, bool vec, const LaunchCtx &ctx) {
             // launch below); the overlap of one's loads with the other's epilogue weighs more
             // the shorter the depth (measured against 256x128 at 9 .. 72 slices).
             // (filters larger than 1x1 gain less: 0.92-0.95 measured at 18 and 36 slices)
+            // Two workgroups of 32x32 per CU against one of 64x64: 3x3 512 -> 512 on 14x14 at batch 5 15 against
+            // 19 us, 128 -> 128 on 28x28 even.
+            if (i == 14 && p.R * p.S > 1 && nk >= 18) eff = 0.30;
             if (i == 0 && sk == 1 && tiles > n_cu) eff = std::min(1.2, 0.90 + (p.R * p.S == 1 ? 3.0 : 0.6) / nk);
             const double cost = static_cast<double>(per_cu) * t.bm * t.bn * share / eff;
             if ((o == 0 && sk == 1) || cost < best_cost) {
@@ -198,18 +206,6 @@ Choice choose_kernel(const ConvParams &p, bool vec, const LaunchCtx &ctx) {
                 best_split = sk;
                 best_cost = cost;
             }
-        }
-    }
-    // Filters larger than 1x1 on very few tiles: the two producers of the 64x64 tile, which locate every
-    // tap of their pixels themselves, are what such a launch waits for; 64x128 has four and half as
-    // many rows per producer.  Measured on MI355X with at most an eighth as many 64x64 tiles as CUs
-    // (3x3 stride 2 at batch 1, SSD's last feature maps): 64x128 is 7-10 % faster; from 56 tiles on
-    // 256 CUs on it is the other way round or even.
-    if (forced < 0 && best == 3 && best_split == 1 && p.R * p.S > 1) {
-        const long long tiles3 = 1LL * ((p.M + 63) / 64) * ((p.K + 63) / 64);
-        if (8 * tiles3 <= n_cu) {
-            best = 2;
-            best_cost = static_cast<double>(64 * 128) / 0.72;   // one round of 64x128 at its table efficiency
         }
     }
     if (forced >= 0 && forced < GPULET_CONV_TILES) {
@@ -233,19 +229,18 @@ Choice choose_kernel(const ConvParams &p, bool vec, const LaunchCtx &ctx) {
     const bool patch_ok = patch_eligible(p, vec, &tw);
     if (best == 7 && !patch_ok) best = 1;  // the patch kernel does not apply: same tile shape, gathered
     // The patch kernel runs one workgroup per CU.  Measured on MI355X it beats the gathering
-    // tiles whenever all of its workgroups are resident at once (a second round doubles its
+    // tiles whenever all of its 128x64 workgroups are resident at once (a second round doubles its
     // time), from a single block of 64 channels on: 3x3 64 -> 64 on 56x56 at batch 8 5.5 against
     // 6.2 us, 128 -> 256 on 14x14 at batch 32 6.9 against 7.8, 192 -> 384 on 7x7 7.9 against 10.0.
+    // patch_variant() then says whether smaller tiles spread it better.
+    int patch_tile = 0;
     if (forced < 0 && patch_ok) {
-        const int n_cb = (p.Q + tw - 1) / tw;
-        const long long lin = 1LL * p.N * p.P * tw;
-        const long long tiles = ((lin + PATCH_BM - 1) / PATCH_BM) * n_cb * ((p.K + 63) / 64);
-        // Workgroups are dealt round-robin to 8 dies and, inside a die, to 4 shader engines; a
-        // CU holds one workgroup, so every shader engine must have a CU for each of its share.
-        const long long per_se = ((tiles + 7) / 8 + 3) / 4;
-        if (per_se <= n_cu / 32) {
+        bool one_round = false;
+        const int v = patch_variant(p, tw, n_cu, &one_round);
+        if (one_round) {
             best = 7;
             best_split = 1;
+            patch_tile = v;
         }
     }
     if (best == 8 && !stream_applicable(p, vec)) best = 2;  // same tile shape, one tile per workgroup
@@ -266,7 +261,7 @@ Choice choose_kernel(const ConvParams &p, bool vec, const LaunchCtx &ctx) {
     if (best == 9 && !stem_applicable(p)) best = 1;
     if (forced < 0 && stem_applicable(p)) best = 9;  // by shape alone: the same bits in every batch and gpu-let
     if (best == 11 && !tall_ok) best = 1;
-    return Choice{best, best_split, tw, tw64, th11, tw11, (is_gathering_tile(best) || best == 11) ? best_cost : 0.0};
+    return Choice{best, best_split, tw, tw64, th11, tw11, patch_tile, (is_gathering_tile(best) || best == 11) ? best_cost : 0.0};
 }
 
 }  // namespace
@@ -299,7 +294,7 @@ hipError_t launch_conv(const ConvArgs &a, const LaunchCtx &ctx, hipStream_t stre
         case 10: return launch_c64(p, c.tw64, n_cu, false, stream);
         case 9: return launch_stem(p, n_cu, stream);
         case 8: return launch_stream(p, n_cu, stream);
-        case 7: return launch_patch(p, c.tw, stream);
+        case 7: return launch_patch(p, c.tw, c.patch_tile, stream);
         default: {
             const long long tiles128 = 1LL * ((p.M + 127) / 128) * ((p.K + 127) / 128);
             return launch_igemm(p, vec, c.best, c.split, tiles128 > n_cu, stream);

@@ -20,6 +20,7 @@ namespace conv {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 constexpr int BK = 64;         // depth slice per main-loop step (elements)
 constexpr int CHUNK = 8;       // elements per 16-byte chunk
@@ -156,6 +157,32 @@ __device__ __forceinline__ int tile_of_block(const ConvParams &p) { return tile_
 
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 
+// The two bf16 matrix instructions.  32x32x16 holds one 32-row fragment pair per 16 channels;
+// 16x16x32 covers 32 channels per issue on a quarter of the tile, so that four wavefronts can
+// share a 32x32 tile and the serial chain of a deep, small tile is a quarter as long.  Both add
+// the products of a lane's chain in the same order: a sum has the same bits either way.
+template <int MF>
+struct Mma;
+template <>
+struct Mma<32> {
+    typedef f32x16 Acc;
+    static constexpr int NV = 16, KSTEP = 16;   // accumulator registers, depth of one instruction
+    static __device__ __forceinline__ Acc mul(const bf16x8 a, const bf16x8 b, const Acc c) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+    }
+    // tile row that accumulator register v of a lane holds (the column is lane % MF)
+    static __device__ __forceinline__ int row(int v, int lane) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
+};
+template <>
+struct Mma<16> {
+    typedef f32x4 Acc;
+    static constexpr int NV = 4, KSTEP = 32;
+    static __device__ __forceinline__ Acc mul(const bf16x8 a, const bf16x8 b, const Acc c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int v, int lane) { return 4 * (lane >> 4) + v; }
+};
+
 // s_waitcnt immediate that waits until at most n vector-memory operations are
 // outstanding and leaves the other counters alone (gfx9 encoding).
 constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
@@ -186,6 +213,16 @@ __device__ __forceinline__ void dma16(const i32x4 rsrc, unsigned lds_base, unsig
                  :
                  : "s"(lds_base), "v"(voff), "s"(rsrc)
                  : "memory");
+}
+
+// The same at LDS address `lds_base` + IMM (one scalar addition straight into M0), with a scalar
+// byte offset `soff` added to every lane's.  A lane whose `voff` has the OOB bit reads zeros whatever
+// soff is below the buffer's size.
+__device__ __forceinline__ void dma16(const i32x4 rsrc, unsigned lds_base, const int imm, unsigned voff, int soff) {
+    asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(lds_base), "v"(voff), "s"(rsrc), "s"(soff), "n"(imm)
+                 : "memory", "scc");
 }
 
 // Last step of the epilogue for a BM x BN fp32 tile parked in LDS (rows padded
@@ -328,8 +365,10 @@ hipError_t launch_igemm(const ConvParams &p, bool vec, int tile, int split_k, bo
 hipError_t launch_igemm_group(const ConvParams *p, int n, int tile, bool two_stage, hipStream_t stream);
 
 // conv_patch.hip: tile 7 (input patch in LDS) and tile 10 (64 input channels, weights in registers).
+// `variant`: index into kPatchTiles; the automatic choice takes the one patch_variant() names.
 bool patch_eligible(const ConvParams &p, bool vec, int *tw_out);
-hipError_t launch_patch(ConvParams p, int tw, hipStream_t stream);
+int patch_variant(const ConvParams &p, int tw, int n_cu, bool *one_round);
+hipError_t launch_patch(ConvParams p, int tw, int variant, hipStream_t stream);
 bool c64_applicable(const ConvParams &p, bool vec, int *tw_out, bool pool2 = false);
 hipError_t launch_c64(ConvParams p, int tw, int n_cu, bool pool2, hipStream_t stream);
 

@@ -65,8 +65,10 @@ __device__ __forceinline__ void store_tile(const ConvParams &p, const f32x16 (&a
 }
 
 // ---------------------------------------------------------------------------
-// Main kernel: C % 8 == 0.  POINTWISE = 1x1 filter without padding (no bounds
-// tests at all; a strided 1x1 is pointwise too).
+// Main kernel: C % 8 == 0.  How an instance walks the depth (Depth): POINT = 1x1 filter
+// without padding (no bounds tests at all; a strided 1x1 is pointwise too); TAPS = 64-channel
+// blocks with the filter taps inside; LINEAR = (r, s, c), any C; MIXED = TAPS or LINEAR as the
+// layer asks (launch groups).
 //
 // Staging uses buffer loads that write straight into LDS (no registers, no
 // ds_write): one wavefront instruction moves 64 x 16 bytes into a contiguous
@@ -78,6 +80,19 @@ __device__ __forceinline__ void store_tile(const ConvParams &p, const f32x16 (&a
 // are in flight.
 // ---------------------------------------------------------------------------
 
+enum class Depth { POINT, TAPS, LINEAR, MIXED };
+
+// LDS elements of an instance: the ring, or the fp32 tile of the epilogue (rows padded by 8 floats).
+constexpr int ring_elems(int bm, int bn, int ns, int spb) {
+    return std::max(ns * spb * (bm + bn) * BK, bm * (bn + 8) * 2);
+}
+// Wavefronts per SIMD that the registers must leave room for: as many workgroups as LDS holds.  (At 84
+// registers instead of 80 a CU held one 128x64 workgroup instead of two: 3x3 64 -> 64 on 56x56 at
+// batch 32 19 -> 22.7 us.)
+constexpr int waves_per_simd(int bm, int bn, int ns, int spb, int waves) {
+    return std::min(8, std::max(1, 160 * 1024 / (ring_elems(bm, bn, ns, spb) * 2 + 512)) * waves / 4);
+}
+
 // Wavefronts are specialised.  The first CWM x CWN wavefronts ("consumers")
 // only read LDS and issue MFMAs; the last NPROD wavefronts ("producers") only
 // compute addresses and issue transfers.  A wavefront blocked on a saturated
@@ -86,22 +101,27 @@ __device__ __forceinline__ void store_tile(const ConvParams &p, const f32x16 (&a
 // transfers of slice j, after it the stage slice j-1 occupied is free again.
 // EXTRA: the layer has a second destination or a pooling side job (1x1 layers only); layers
 // without either run the instance that knows of neither.
-template <int BM, int BN, int CWM, int CWN, int NPROD, int NS, bool POINTWISE, bool EXTRA>
+// SPLIT: the layer's depth is split over workgroups.
+// MF: edge of the matrix instruction's tile.  SPB: depth slices per ring stage and barrier.  Launches
+// whose tiles do not even fill the CUs are bound by the step from one barrier to the next, not by
+// the matrix pipeline: the 32x32 tile takes two slices per barrier.
+template <int BM, int BN, int CWM, int CWN, int NPROD, int NS, Depth DEPTH, bool EXTRA, bool SPLIT, int MF, int SPB>
 __device__ __forceinline__ void conv_igemm_body(const ConvParams &p, const int bid) {
     constexpr int NCONS = CWM * CWN;
     constexpr int WM = BM / CWM, WN = BN / CWN;  // consumer wavefront tile
-    constexpr int MT = WM / 32, NT = WN / 32;    // MFMA tiles per consumer
-    static_assert(MT >= 1 && NT >= 1 && WM % 32 == 0 && WN % 32 == 0, "tile shape");
+    constexpr int MT = WM / MF, NT = WN / MF;    // MFMA tiles per consumer
+    static_assert(MT >= 1 && NT >= 1 && WM % MF == 0 && WN % MF == 0, "tile shape");
+    typedef Mma<MF> MM;
     static_assert(NPROD == 2 || NPROD == 4, "swizzle key must not depend on the instruction index");
     constexpr int PROWS = NPROD * 8;                       // tile rows one round of producer instructions fills
     constexpr int AINS = BM / PROWS, BINS = BN / PROWS;    // transfers per producer lane and slice
     static_assert(BM % PROWS == 0 && BN % PROWS == 0, "tile rows per producer round");
-    constexpr int STAGE = (BM + BN) * BK;                  // elements per LDS stage: A rows, then B rows
-    static_assert(NS >= 2 && (AINS + BINS) * (NS - 2) <= 63, "ring depth vs the 6-bit transfer counter");
+    constexpr int SLICE = (BM + BN) * BK;                  // elements per depth slice: A rows, then B rows
+    constexpr int STAGE = SLICE * SPB;                     // elements per LDS stage
+    static_assert(NS >= 2 && (AINS + BINS) * SPB * (NS - 2) <= 63, "ring depth vs the 6-bit transfer counter");
 
     constexpr int LDT = BN + 8;  // padded row of the fp32 epilogue tile that reuses the ring
-    constexpr int RING = NS * STAGE > BM * LDT * 2 ? NS * STAGE : BM * LDT * 2;
-    __shared__ __attribute__((aligned(1024))) __bf16 ring[RING];
+    __shared__ __attribute__((aligned(1024))) __bf16 ring[ring_elems(BM, BN, NS, SPB)];
 
     // Split-K: consecutive work items share an output tile and each takes a
     // contiguous range of depth slices.
@@ -111,14 +131,14 @@ __device__ __forceinline__ void conv_igemm_body(const ConvParams &p, const int b
     // workgroup with a tile does not wait for one more field of the argument block first.
     fetch_params(p);
     const int item = tile_of_block(p, bid);
-    if (item >= p.n_tiles * p.split_k || bid >= p.tiles_per_xcd * 8) {
+    if (item >= p.n_tiles * (SPLIT ? p.split_k : 1) || bid >= p.tiles_per_xcd * 8) {
         if (EXTRA && bid >= p.tiles_per_xcd * 8 && p.side_blocks > 0) {
             const int idx = (bid - p.tiles_per_xcd * 8) * ((CWM * CWN + NPROD) * 64) + static_cast<int>(threadIdx.x);
             if (idx < p.side_pool.total) pool_max_item<3>(p.side_pool, idx);
         }
         return;
     }
-    const int tile = fdiv(item, p.d_split_k), ks = item - tile * p.split_k;
+    const int tile = SPLIT ? fdiv(item, p.d_split_k) : item, ks = SPLIT ? item - tile * p.split_k : 0;
     const int tm = fdiv(tile, p.d_tiles_n), tn = tile - tm * p.tiles_n;
     const int m0 = tm * BM, n0 = tn * BN;
     const BiasRegs bias_regs = load_bias<BN, (CWM * CWN + NPROD) * 64>(p, n0);
@@ -126,16 +146,17 @@ __device__ __forceinline__ void conv_igemm_body(const ConvParams &p, const int b
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nk_all = (p.Kg + BK - 1) / BK;
-    const int k_first = ks * p.sps;                                  // first slice of this workgroup
-    const int nk = max(0, min(nk_all, k_first + p.sps) - k_first);  // slices of this workgroup
+    const int k_first = SPLIT ? ks * p.sps : 0;                      // first slice of this workgroup
+    const int nk = SPLIT ? max(0, min(nk_all, k_first + p.sps) - k_first) : nk_all;  // slices of this workgroup
+    const int nst = (nk + SPB - 1) / SPB;                            // ring stages they fill
 
-    f32x16 acc[MT][NT];  // consumers only
+    typename MM::Acc acc[MT][NT];  // consumers only
 
     if (wave >= NCONS) {
         // ------------------------------------------------------------ producer
         const int pw = wave - NCONS;
-        const i32x4 rx = make_rsrc(p.x, p.x_bytes);
         const i32x4 rw = make_rsrc(p.w, p.w_bytes);
+        const unsigned ring_lds = lds_addr(ring);
 
         // Instruction u of this wavefront fills tile rows u*PROWS + pw*8 .. +8;
         // this lane fills physical chunk lane&7 of row u*PROWS + lrow, i.e.
@@ -143,8 +164,9 @@ __device__ __forceinline__ void conv_igemm_body(const ConvParams &p, const int b
         const int lrow = pw * 8 + (lane >> 3);
         const int cc = (lane & 7) ^ ((lrow >> 1) & 7);
 
-        // Byte offset of tap (0, 0), channel 0 of each pixel row (may be negative
-        // before the tap offset is added), and the pixel's top-left corner.
+        // Byte offset of tap (0, 0) of each pixel row, counted from `before` bytes in front of x so
+        // that it is never negative, and the pixel's top-left corner.
+        const int before = ((p.pad * p.W + p.pad) * p.ldx * 2 + 255) & ~255;
         int a_off[AINS], a_h0[AINS], a_w0[AINS];
 #pragma unroll
         for (int i = 0; i < AINS; ++i) {
@@ -155,7 +177,7 @@ __device__ __forceinline__ void conv_igemm_body(const ConvParams &p, const int b
                 const int pp = fdiv(pq, p.d_q), qq = pq - pp * p.Q;
                 a_h0[i] = pp * p.stride - p.pad;
                 a_w0[i] = qq * p.stride - p.pad;
-                a_off[i] = (((n * p.H + a_h0[i]) * p.W + a_w0[i]) * p.ldx) * 2;
+                a_off[i] = (((n * p.H + a_h0[i]) * p.W + a_w0[i]) * p.ldx) * 2 + before;
             } else {
                 a_h0[i] = -(1 << 28);  // fails every bounds test
                 a_w0[i] = -(1 << 28);
@@ -169,172 +191,261 @@ __device__ __forceinline__ void conv_igemm_body(const ConvParams &p, const int b
             b_off[i] = k < p.K ? static_cast<unsigned>((k * p.Kg + cc * CHUNK) * 2) : OOB;
         }
 
-        // Depth position of the chunk this lane fetches next: element index g, its
-        // filter tap (r, s), channel c, and the tap's byte offset inside the image.
-        // With dense pixels (ldx == C) advancing s by one and c by -C leaves the
-        // address unchanged (a filter row covers a contiguous span of the image row),
-        // so the offset only jumps when the filter moves to its next row; when the
-        // layer reads a channel slice of wider pixels it also skips ldx - C elements
-        // from one pixel to the next.
-        //
-        // Two depth orders.  Linear: g runs through (r, s, c) as the weights are
-        // stored.  Tap-inner (C a multiple of 64, filter larger than 1x1): for each
-        // block of 64 channels all taps follow one another, so the image rows a
-        // workgroup just fetched for one tap are fetched again for the next while
-        // they are still in the nearest cache.  Both operands use the same order,
-        // so only the summation order of the result changes.
-        int g, r, s, c, tap, cblk = 0, issued = 0;
-        if (!POINTWISE && p.tap_inner) {
-            const int rs = p.R * p.S;
-            const int cb = k_first / rs, t = k_first - cb * rs;
-            r = fdiv(t, p.d_s);
-            s = t - r * p.S;
-            cblk = cb * BK;
-            c = cblk + cc * CHUNK;
-            g = t * p.C + c;
-            tap = ((r * p.W + s) * p.ldx + c) * 2;
-        } else {
-            g = k_first * BK + cc * CHUNK;
-            const int t = fdiv(g, p.d_c);
-            c = g - t * p.C;
-            r = fdiv(t, p.d_s);
-            s = t - r * p.S;
-            tap = ((r * p.W + s) * p.ldx + c) * 2;
-        }
-        auto normalise = [&]() {
-            while (c >= p.C) {
-                c -= p.C;
-                tap += (p.ldx - p.C) * 2;  // nothing when the pixels are dense
-                if (++s == p.S) {
-                    s = 0;
-                    ++r;
-                    tap += (p.W - p.S) * p.ldx * 2;
+        // The transfers of one depth slice: lane offsets into x and w, the scalar offsets added to
+        // them, the buffers.
+        struct Slice {
+            unsigned a[AINS], b[BINS];
+            int xs, ws;
+            i32x4 rx, rw;
+        };
+        // Walks the depth.  next(slice) works out the transfers of the next slice and advances the
+        // depth position; slices past the end of the depth transfer zeros: they change no sum, or
+        // nobody reads them.  Step j waits for this lane's transfers of stage j (those of the NS-2
+        // later stages may stay in flight), meets everybody, and refills the LDS stage j-1 was read
+        // from with stage j+NS-1.  What it refills with is worked out in front of the barrier (the
+        // empty asm statements keep the compiler from moving it behind), so that the transfers
+        // follow the barrier at once; with two slices per barrier the consumers' reads of the stage
+        // want that time (3x3 512 -> 512, 14x14, stride 2, batch 1: 8.5 us so, 8.8 the other way).  The loop is not unrolled: a launch starts with cold instruction caches, and
+        // the producers' code has to be short.
+        auto run = [&](auto &&next) {
+            constexpr bool EARLY = SPB == 1;
+            unsigned base = ring_lds + pw * 8 * (BK * 2);
+            const unsigned end = base + NS * STAGE * 2;
+            Slice sl;
+            if (EARLY) next(sl);
+#pragma unroll 1
+            for (int j = 1 - NS; j < nst; ++j) {
+                if (EARLY) {
+                    asm volatile("" : "+s"(sl.xs), "+s"(sl.ws), "+s"(base));
+#pragma unroll
+                    for (int i = 0; i < AINS; ++i) asm volatile("" : "+v"(sl.a[i]));
                 }
+                if (j >= 0) {
+                    __builtin_amdgcn_s_waitcnt(vmcnt_imm((AINS + BINS) * SPB * (NS - 2)));
+                    __syncthreads();
+                }
+#pragma unroll
+                for (int h = 0; h < SPB; ++h) {
+                    if (!EARLY) next(sl);
+#pragma unroll
+                    for (int i = 0; i < AINS; ++i) dma16(sl.rx, base, h * SLICE * 2 + i * PROWS * (BK * 2), sl.a[i], sl.xs);
+#pragma unroll
+                    for (int i = 0; i < BINS; ++i) dma16(sl.rw, base, h * SLICE * 2 + (BM + i * PROWS) * (BK * 2), sl.b[i], sl.ws);
+                    if (EARLY) next(sl);
+                }
+                base += STAGE * 2;
+                if (base == end) base -= NS * STAGE * 2;
             }
         };
 
-        // Starts the transfer of the next depth slice into `stage` and advances the
-        // position.  Slices past the end of the depth transfer zeros nobody reads.
-        auto issue_next = [&](const __bf16 *stage) {
-            const bool g_ok = issued < nk && g < p.Kg;
-            unsigned base = lds_addr(stage) + pw * 8 * (BK * 2);
+        // Whether tap t of a row lies outside the image: bit t of a mask, made once by repeating the
+        // mask of valid filter columns for every valid filter row with one multiplication.  For
+        // filters of up to 31 taps; bit 31 is always set.
+        auto taps_outside = [&](unsigned (&out)[AINS]) {
+            unsigned rows = 0;   // bit r * S of every filter row r
+            for (int i = 0; i < p.R; ++i) rows |= 1u << (i * p.S);
 #pragma unroll
             for (int i = 0; i < AINS; ++i) {
-                bool ok = g_ok;
-                if (!POINTWISE)
-                    ok = ok & ((unsigned)(a_h0[i] + r) < (unsigned)p.H) & ((unsigned)(a_w0[i] + s) < (unsigned)p.W);
-                const unsigned off = ok ? static_cast<unsigned>(a_off[i] + tap) : OOB;
-                dma16(rx, base + i * PROWS * (BK * 2), off);
+                const int r_lo = max(0, -a_h0[i]), r_hi = min(p.R, p.H - a_h0[i]);
+                const int s_lo = max(0, -a_w0[i]), s_hi = min(p.S, p.W - a_w0[i]);
+                unsigned in = 0;
+                if (r_lo < r_hi && s_lo < s_hi && a_h0[i] > -(1 << 28))
+                    in = ((1u << s_hi) - (1u << s_lo)) * (((rows & ((1u << (r_hi * p.S)) - 1u)) >> (r_lo * p.S)) << (r_lo * p.S));
+                out[i] = ~in;
             }
-            base += BM * (BK * 2);
+        };
+
+        // Depth orders.  Linear: (r, s, c) as the weights are stored.  Tap-inner (C a multiple of 64):
+        // for each block of 64 channels all taps follow one another, so the image rows a workgroup
+        // just fetched for one tap are fetched again for the next while they are still in the
+        // nearest cache.  Both operands use the same order, so only the summation order of the
+        // result changes.
+        //
+        // Tap-inner and 1x1: the depth position is the same for all lanes, so it travels as the
+        // transfers' scalar offset and a lane's own offsets never change.  That leaves two vector
+        // instructions per pixel row (one for 1x1, none per filter row) next to the transfer; with
+        // one wavefront per SIMD these instructions bound small tiles (per-lane depth positions:
+        // 0.15 us per slice of a 32x32 tile on 3x3 512 -> 512, 14x14, stride 2, against 0.06 for 1x1).
+        if (DEPTH == Depth::POINT) {
+            const i32x4 rx = make_rsrc(p.x, p.x_bytes);
+            int left = p.C - k_first * BK, soff = k_first * BK * 2;   // k_first < nk_all
+            const int cc8 = cc * CHUNK;
+            run([&](Slice &sl) {
+                // lanes past the last channel, and all lanes past the last slice, transfer zeros
+                const unsigned past = cc8 < left ? 0u : OOB;
+                sl.rx = rx;
+                sl.rw = rw;
+                sl.xs = sl.ws = left > 0 ? soff : 0;
 #pragma unroll
-            for (int i = 0; i < BINS; ++i) {
-                const unsigned off = g_ok ? b_off[i] + static_cast<unsigned>(g - cc * CHUNK) * 2u : OOB;
-                dma16(rw, base + i * PROWS * (BK * 2), off);
-            }
-            ++issued;
-            if (!POINTWISE && p.tap_inner) {
-                g += p.C;
-                tap += p.ldx * 2;
+                for (int i = 0; i < AINS; ++i) sl.a[i] = static_cast<unsigned>(a_off[i] + cc8 * 2) | past;
+#pragma unroll
+                for (int i = 0; i < BINS; ++i) sl.b[i] = b_off[i] | past;
+                left -= BK;
+                soff += BK * 2;
+            });
+        } else if (DEPTH == Depth::TAPS || (DEPTH == Depth::MIXED && p.tap_inner)) {
+            // The hardware may subtract the scalar offset from the size before it compares: the size
+            // covers the largest one (lanes whose tap is inside the image stay inside x by the mask).
+            const unsigned x_size = p.x_bytes + before + (((p.R - 1) * p.W + p.S - 1) * p.ldx + p.C) * 2;
+            const i32x4 rx = make_rsrc(reinterpret_cast<const char *>(p.x) - before, x_size);
+            const int rs = p.R * p.S;
+            const int cb = k_first / rs;
+            int t = k_first - cb * rs, r = fdiv(t, p.d_s), s = t - r * p.S, c2 = cb * BK * 2;
+            int xo = (r * p.W + s) * p.ldx * 2 + c2, wo = t * p.C * 2 + c2, left = nk;
+            unsigned out[AINS];
+            taps_outside(out);
+#pragma unroll
+            for (int i = 0; i < AINS; ++i) a_off[i] += cc * (CHUNK * 2);
+            run([&](Slice &sl) {
+                const bool ok = left > 0;
+                sl.rx = rx;
+                sl.rw = rw;
+                sl.rx[2] = ok ? static_cast<int>(x_size) : 0;   // past the last slice everything is out of range
+                sl.rw[2] = ok ? static_cast<int>(p.w_bytes) : 0;
+                sl.xs = ok ? xo : 0;
+                sl.ws = ok ? wo : 0;
+#pragma unroll
+                for (int i = 0; i < AINS; ++i) sl.a[i] = ((out[i] << (31 - t)) & OOB) | static_cast<unsigned>(a_off[i]);
+#pragma unroll
+                for (int i = 0; i < BINS; ++i) sl.b[i] = b_off[i];
+                --left;
+                ++t;
+                wo += p.C * 2;
+                xo += p.ldx * 2;
                 if (++s == p.S) {
                     s = 0;
-                    tap += (p.W - p.S) * p.ldx * 2;
+                    xo += (p.W - p.S) * p.ldx * 2;
                     if (++r == p.R) {
-                        r = 0;
-                        cblk += BK;
-                        g = cblk + cc * CHUNK;
-                        tap = g * 2;
+                        r = t = 0;
+                        c2 += BK * 2;
+                        xo = wo = c2;
                     }
                 }
-            } else {
+            });
+        } else {
+            // Depth position of the chunk this lane fetches next: element index g, its filter tap
+            // (r, s), channel c, and the tap's byte offset inside the image.  With dense pixels
+            // (ldx == C) advancing s by one and c by -C leaves the address unchanged (a filter row
+            // covers a contiguous span of the image row), so the offset only jumps when the filter
+            // moves to its next row; when the layer reads a channel slice of wider pixels it also
+            // skips ldx - C elements from one pixel to the next.
+            const i32x4 rx = make_rsrc(p.x, p.x_bytes);
+            int g = k_first * BK + cc * CHUNK, issued = 0;
+            const int t = fdiv(g, p.d_c);
+            int c = g - t * p.C, r = fdiv(t, p.d_s), s = t - r * p.S;
+            int tap = ((r * p.W + s) * p.ldx + c) * 2 - before;
+            auto issue_slice = [&](unsigned base) {
+                const bool g_ok = issued < nk && g < p.Kg;
+                base += pw * 8 * (BK * 2);
+#pragma unroll
+                for (int i = 0; i < AINS; ++i) {
+                    const bool ok = g_ok & ((unsigned)(a_h0[i] + r) < (unsigned)p.H) & ((unsigned)(a_w0[i] + s) < (unsigned)p.W);
+                    dma16(rx, base + i * PROWS * (BK * 2), ok ? static_cast<unsigned>(a_off[i] + tap) : OOB);
+                }
+                base += BM * (BK * 2);
+#pragma unroll
+                for (int i = 0; i < BINS; ++i) {
+                    const unsigned off = g_ok ? b_off[i] + static_cast<unsigned>(g - cc * CHUNK) * 2u : OOB;
+                    dma16(rw, base + i * PROWS * (BK * 2), off);
+                }
+                ++issued;
                 g += BK;
                 c += BK;
                 tap += BK * 2;
-                if (!POINTWISE) normalise();
+                while (c >= p.C) {
+                    c -= p.C;
+                    tap += (p.ldx - p.C) * 2;  // nothing when the pixels are dense
+                    if (++s == p.S) {
+                        s = 0;
+                        ++r;
+                        tap += (p.W - p.S) * p.ldx * 2;
+                    }
+                }
+            };
+            // The ring position is a compile-time constant inside the unrolled body (rolled up like the
+            // other orders, this one lost a fifth on 3x3 160 -> 320, 14x14, batch 32).
+            auto issue_stage = [&](int stage) {
+#pragma unroll
+                for (int i = 0; i < SPB; ++i) issue_slice(ring_lds + (stage * STAGE + i * SLICE) * 2);
+            };
+#pragma unroll
+            for (int i = 0; i < NS - 1; ++i) issue_stage(i);
+            auto step = [&](int refill) {
+                __builtin_amdgcn_s_waitcnt(vmcnt_imm((AINS + BINS) * SPB * (NS - 2)));
+                __syncthreads();
+                issue_stage(refill);
+            };
+            int kt = 0;
+            for (; kt + NS <= nst; kt += NS) {
+#pragma unroll
+                for (int u = 0; u < NS; ++u) step((u + NS - 1) % NS);
             }
-        };
-
-        // Step j: wait for this lane's transfers of slice j (those of the NS-2 later
-        // slices may stay in flight), meet everybody, refill the stage slice j-1 was
-        // read from with slice j+NS-1.
 #pragma unroll
-        for (int i = 0; i < NS - 1; ++i) issue_next(ring + i * STAGE);
-        auto step = [&](int refill) {
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm((AINS + BINS) * (NS - 2)));
-            __syncthreads();
-            issue_next(ring + refill * STAGE);
-        };
-        // The ring position is a compile-time constant inside the unrolled body.
-        int kt = 0;
-        for (; kt + NS <= nk; kt += NS) {
-#pragma unroll
-            for (int u = 0; u < NS; ++u) step((u + NS - 1) % NS);
+            for (int u = 0; u < NS - 1; ++u)
+                if (kt + u < nst) step((u + NS - 1) % NS);
         }
-#pragma unroll
-        for (int u = 0; u < NS - 1; ++u)
-            if (kt + u < nk) step((u + NS - 1) % NS);
         // Every transfer has landed before the ring is reused by the epilogue.
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     } else {
     // ---------------------------------------------------------------- consumer
     const int wy = wave / CWN, wx = wave - wy * CWN;
-    const int frow = lane & 31;   // row of an MFMA operand this lane supplies
-    const int fhalf = lane >> 5;  // which 8 of the 16 depth elements of a step
+    const int frow = lane & (MF - 1);  // row of an MFMA operand this lane supplies
+    const int fpart = lane / MF;       // which 8 of the depth elements of a step
 
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+            for (int v = 0; v < MM::NV; ++v) acc[i][j][v] = 0.f;
 
     auto step = [&](int cur) {
         __syncthreads();
-        const __bf16 *sA = ring + cur * STAGE, *sB = sA + BM * BK;
-        constexpr int KS = BK / 16;
+        constexpr int KS = BK / MM::KSTEP, CPS = MM::KSTEP / CHUNK;   // depth steps of a slice, chunks of a step
         if constexpr (MT * NT == 1) {
             // One matrix instruction per pair of fragment reads: the wavefront would wait out the
-            // LDS latency before each of them.  All reads of the slice are issued first, and the
+            // LDS latency before each of them.  All reads of the stage are issued first, and the
             // scheduling barrier keeps them there; each matrix instruction then waits only for its
-            // own operands, and the compiler moves the next slice's barrier and reads up between
-            // this slice's last matrix instructions.  (With more accumulators per wavefront the
+            // own operands, and the compiler moves the next stage's barrier and reads up between
+            // this stage's last matrix instructions.  (With more accumulators per wavefront the
             // extra fragment registers cost more than the latency: measured slower.)
-            bf16x8 fa[KS], fb[KS];
+            bf16x8 fa[SPB * KS], fb[SPB * KS];
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                fa[ks] = *reinterpret_cast<const bf16x8 *>(&sA[lds_pos(wy * WM + frow, ks * 2 + fhalf)]);
-                fb[ks] = *reinterpret_cast<const bf16x8 *>(&sB[lds_pos(wx * WN + frow, ks * 2 + fhalf)]);
+            for (int i = 0; i < SPB * KS; ++i) {
+                const __bf16 *sA = ring + cur * STAGE + (i / KS) * SLICE, *sB = sA + BM * BK;
+                fa[i] = *reinterpret_cast<const bf16x8 *>(&sA[lds_pos(wy * WM + frow, (i % KS) * CPS + fpart)]);
+                fb[i] = *reinterpret_cast<const bf16x8 *>(&sB[lds_pos(wx * WN + frow, (i % KS) * CPS + fpart)]);
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks], fb[ks], acc[0][0], 0, 0, 0);
+            for (int i = 0; i < SPB * KS; ++i) acc[0][0] = MM::mul(fa[i], fb[i], acc[0][0]);
         } else {
+            static_assert(SPB == 1, "several slices per barrier: one accumulator tile per wavefront");
+            const __bf16 *sA = ring + cur * STAGE, *sB = sA + BM * BK;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 bf16x8 fa[MT], fb[NT];
 #pragma unroll
                 for (int i = 0; i < MT; ++i)
-                    fa[i] = *reinterpret_cast<const bf16x8 *>(&sA[lds_pos(wy * WM + i * 32 + frow, ks * 2 + fhalf)]);
+                    fa[i] = *reinterpret_cast<const bf16x8 *>(&sA[lds_pos(wy * WM + i * MF + frow, ks * CPS + fpart)]);
 #pragma unroll
                 for (int j = 0; j < NT; ++j)
-                    fb[j] = *reinterpret_cast<const bf16x8 *>(&sB[lds_pos(wx * WN + j * 32 + frow, ks * 2 + fhalf)]);
+                    fb[j] = *reinterpret_cast<const bf16x8 *>(&sB[lds_pos(wx * WN + j * MF + frow, ks * CPS + fpart)]);
 #pragma unroll
                 for (int i = 0; i < MT; ++i)
 #pragma unroll
-                    for (int j = 0; j < NT; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+                    for (int j = 0; j < NT; ++j) acc[i][j] = MM::mul(fa[i], fb[j], acc[i][j]);
             }
         }
     };
     int kt = 0;
-    for (; kt + NS <= nk; kt += NS) {
+    for (; kt + NS <= nst; kt += NS) {
 #pragma unroll
         for (int u = 0; u < NS; ++u) step(u);
     }
 #pragma unroll
     for (int u = 0; u < NS - 1; ++u)
-        if (kt + u < nk) step(u);
+        if (kt + u < nst) step(u);
 
     }
 
@@ -350,15 +461,14 @@ __device__ __forceinline__ void conv_igemm_body(const ConvParams &p, const int b
     __syncthreads();  // all LDS reads of the main loop are done, all transfers have landed
     if (wave < NCONS) {
         const int wy = wave / CWN, wx = wave - wy * CWN;
-        const int frow = lane & 31, fhalf = lane >> 5;
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
-            const int col = wx * WN + j * 32 + frow;
+            const int col = wx * WN + j * MF + (lane & (MF - 1));
 #pragma unroll
             for (int i = 0; i < MT; ++i)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = wy * WM + i * 32 + 8 * (v >> 2) + 4 * fhalf + (v & 3);
+                for (int v = 0; v < MM::NV; ++v) {
+                    const int row = wy * WM + i * MF + MM::row(v, lane);
                     stg[row * LDT + col] = acc[i][j][v];
                 }
         }
@@ -377,7 +487,7 @@ __device__ __forceinline__ void conv_igemm_body(const ConvParams &p, const int b
     // the counter are accessed with device-scope (cache-bypassing) loads and
     // stores only, and a workgroup waits for its own stores to be acknowledged
     // before it counts itself in.
-    if (p.split_k > 1) {
+    if constexpr (SPLIT) {
         constexpr int DEVICE_SCOPE = 16;  // cache policy sc1: device scope, bypasses the die-local caches
         const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
             p.part, 0, p.n_tiles * p.split_k * (BM * BN * 4), RSRC_FLAGS);
@@ -438,9 +548,9 @@ __device__ __forceinline__ void conv_igemm_body(const ConvParams &p, const int b
     finish_tile<BM, BN, NTHR, EXTRA>(p, stg, n0, bias_regs, [&](int row) { return m0 + row < p.M ? m0 + row : -1; });
 }
 
-template <int BM, int BN, int CWM, int CWN, int NPROD, int NS, bool POINTWISE, bool EXTRA = false>
-__global__ __launch_bounds__((CWM * CWN + NPROD) * 64) void conv_igemm_kernel(const ConvParams p) {
-    conv_igemm_body<BM, BN, CWM, CWN, NPROD, NS, POINTWISE, EXTRA>(p, blockIdx.x);
+template <int BM, int BN, int CWM, int CWN, int NPROD, int NS, Depth DEPTH, bool EXTRA, bool SPLIT, int MF, int SPB>
+__global__ __launch_bounds__((CWM * CWN + NPROD) * 64, waves_per_simd(BM, BN, NS, SPB, CWM * CWN + NPROD)) void conv_igemm_kernel(const ConvParams p) {
+    conv_igemm_body<BM, BN, CWM, CWN, NPROD, NS, DEPTH, EXTRA, SPLIT, MF, SPB>(p, blockIdx.x);
 }
 
 // Several independent layers in one launch (branches of an inception block, a projection
@@ -448,14 +558,14 @@ __global__ __launch_bounds__((CWM * CWN + NPROD) * 64) void conv_igemm_kernel(co
 // index falls into and runs that layer's tile as above.  The general instance serves 1x1
 // members too (its bounds tests always pass for them); when every member is 1x1 the instance
 // without bounds tests is used.  Either way a member's results are the bits of its own launch.
-template <int BM, int BN, int CWM, int CWN, int NPROD, int NS, bool POINTWISE>
-__global__ __launch_bounds__((CWM * CWN + NPROD) * 64) void conv_igemm_group_kernel(const ConvGroup g) {
+template <int BM, int BN, int CWM, int CWN, int NPROD, int NS, Depth DEPTH, int MF, int SPB>
+__global__ __launch_bounds__((CWM * CWN + NPROD) * 64, waves_per_simd(BM, BN, NS, SPB, CWM * CWN + NPROD)) void conv_igemm_group_kernel(const ConvGroup g) {
     const int b = blockIdx.x;
     int j = 0;
 #pragma unroll
     for (int i = 1; i < MAX_GROUP; ++i)
         if (b >= g.first[i]) j = i;
-    conv_igemm_body<BM, BN, CWM, CWN, NPROD, NS, POINTWISE, false>(g.p[j], b - g.first[j]);
+    conv_igemm_body<BM, BN, CWM, CWN, NPROD, NS, DEPTH, false, false, MF, SPB>(g.p[j], b - g.first[j]);
 }
 
 // ---------------------------------------------------------------------------
@@ -598,7 +708,7 @@ __global__ __launch_bounds__(NTHREADS) void conv_igemm_any_kernel(const ConvPara
 
 // CWM x CWN consumers and NPROD producers for the main kernel; the scalar-gather
 // kernel always runs four wavefronts as WGM x WGN.
-template <int BM, int BN, int CWM, int CWN, int NPROD, int NS, int WGM, int WGN>
+template <int BM, int BN, int CWM, int CWN, int NPROD, int NS, int WGM, int WGN, int MF = 32, int SPB = 1>
 hipError_t launch_tile(ConvParams p, bool vec, int split_k, hipStream_t stream) {
     const int tiles_m = (p.M + BM - 1) / BM;
     p.tiles_n = (p.K + BN - 1) / BN;
@@ -615,18 +725,29 @@ hipError_t launch_tile(ConvParams p, bool vec, int split_k, hipStream_t stream) 
     if (p.side_pool.y && !p.side_blocks) return hipErrorInvalidValue;  // nobody would compute the pool
     const dim3 grid(static_cast<unsigned>(p.tiles_per_xcd * 8 + p.side_blocks));
     const dim3 block(THREADS);
+    if constexpr (BM < 64 && BN < 64) {
+        if (!vec) return hipErrorInvalidValue;   // the scalar-gather kernel has no such tile
+    }
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, p); };
+    const bool split = p.split_k > 1;
     if (vec && pointwise && (p.side_blocks > 0 || p.k2 < p.K))
-        hipLaunchKernelGGL((conv_igemm_kernel<BM, BN, CWM, CWN, NPROD, NS, true, true>), grid, block, 0, stream, p);
+        split ? go(conv_igemm_kernel<BM, BN, CWM, CWN, NPROD, NS, Depth::POINT, true, true, MF, SPB>)
+              : go(conv_igemm_kernel<BM, BN, CWM, CWN, NPROD, NS, Depth::POINT, true, false, MF, SPB>);
     else if (vec && pointwise)
-        hipLaunchKernelGGL((conv_igemm_kernel<BM, BN, CWM, CWN, NPROD, NS, true>), grid, block, 0, stream, p);
+        split ? go(conv_igemm_kernel<BM, BN, CWM, CWN, NPROD, NS, Depth::POINT, false, true, MF, SPB>)
+              : go(conv_igemm_kernel<BM, BN, CWM, CWN, NPROD, NS, Depth::POINT, false, false, MF, SPB>);
+    else if (vec && p.tap_inner)
+        split ? go(conv_igemm_kernel<BM, BN, CWM, CWN, NPROD, NS, Depth::TAPS, false, true, MF, SPB>)
+              : go(conv_igemm_kernel<BM, BN, CWM, CWN, NPROD, NS, Depth::TAPS, false, false, MF, SPB>);
     else if (vec)
-        hipLaunchKernelGGL((conv_igemm_kernel<BM, BN, CWM, CWN, NPROD, NS, false>), grid, block, 0, stream, p);
-    else
+        split ? go(conv_igemm_kernel<BM, BN, CWM, CWN, NPROD, NS, Depth::LINEAR, false, true, MF, SPB>)
+              : go(conv_igemm_kernel<BM, BN, CWM, CWN, NPROD, NS, Depth::LINEAR, false, false, MF, SPB>);
+    else if constexpr (BM >= 64 || BN >= 64)
         hipLaunchKernelGGL((conv_igemm_any_kernel<BM, BN, WGM, WGN>), grid, dim3(NTHREADS), 0, stream, p);
     return hipGetLastError();
 }
 
-template <int BM, int BN, int CWM, int CWN, int NPROD, int NS>
+template <int BM, int BN, int CWM, int CWN, int NPROD, int NS, int MF = 32, int SPB = 1>
 hipError_t launch_group_tile(const ConvParams *ps, int n, hipStream_t stream) {
     ConvGroup g;
     int blocks = 0;
@@ -651,9 +772,9 @@ hipError_t launch_group_tile(const ConvParams *ps, int n, hipStream_t stream) {
     g.first[MAX_GROUP] = INT_MAX;
     const dim3 grid(static_cast<unsigned>(blocks)), block((CWM * CWN + NPROD) * 64);
     if (pointwise)
-        hipLaunchKernelGGL((conv_igemm_group_kernel<BM, BN, CWM, CWN, NPROD, NS, true>), grid, block, 0, stream, g);
+        hipLaunchKernelGGL((conv_igemm_group_kernel<BM, BN, CWM, CWN, NPROD, NS, Depth::POINT, MF, SPB>), grid, block, 0, stream, g);
     else
-        hipLaunchKernelGGL((conv_igemm_group_kernel<BM, BN, CWM, CWN, NPROD, NS, false>), grid, block, 0, stream, g);
+        hipLaunchKernelGGL((conv_igemm_group_kernel<BM, BN, CWM, CWN, NPROD, NS, Depth::MIXED, MF, SPB>), grid, block, 0, stream, g);
     return hipGetLastError();
 }
 
@@ -667,11 +788,12 @@ hipError_t launch_igemm_group(const ConvParams *p, int n, int tile, bool two_sta
             return launch_group_tile<128, 128, 4, 2, 4, 3>(p, n, stream);
         case 1: return launch_group_tile<128, 64, 4, 2, 4, 3>(p, n, stream);
         case 2: return launch_group_tile<64, 128, 2, 4, 4, 3>(p, n, stream);
-        case 3: return launch_group_tile<64, 64, 2, 2, 2, 3>(p, n, stream);
+        case 3: return launch_group_tile<64, 64, 2, 2, 4, 3>(p, n, stream);
         case 4: return launch_group_tile<128, 32, 4, 1, 2, 3>(p, n, stream);
         case 5: return launch_group_tile<32, 128, 1, 4, 2, 3>(p, n, stream);
         case 12: return launch_group_tile<192, 128, 2, 4, 4, 3>(p, n, stream);
         case 13: return launch_group_tile<96, 128, 1, 4, 4, 3>(p, n, stream);
+        case 14: return launch_group_tile<32, 32, 2, 2, 4, 3, 16, 2>(p, n, stream);
         default: return launch_group_tile<256, 128, 4, 2, 4, 3>(p, n, stream);
     }
 }
@@ -685,7 +807,7 @@ hipError_t launch_igemm(const ConvParams &p, bool vec, int tile, int split_k, bo
             return launch_tile<128, 128, 4, 2, 4, 3, 2, 2>(p, vec, split_k, stream);
         case 1: return launch_tile<128, 64, 4, 2, 4, 3, 2, 2>(p, vec, split_k, stream);
         case 2: return launch_tile<64, 128, 2, 4, 4, 3, 2, 2>(p, vec, split_k, stream);
-        case 3: return launch_tile<64, 64, 2, 2, 2, 3, 2, 2>(p, vec, split_k, stream);
+        case 3: return launch_tile<64, 64, 2, 2, 4, 3, 2, 2>(p, vec, split_k, stream);
         case 4: return launch_tile<128, 32, 4, 1, 2, 3, 4, 1>(p, vec, split_k, stream);
         case 5: return launch_tile<32, 128, 1, 4, 2, 3, 1, 4>(p, vec, split_k, stream);
         // three row tiles per consumer (96 pixels x 32 filters); the scalar-gather variant has no such
@@ -696,6 +818,9 @@ hipError_t launch_igemm(const ConvParams &p, bool vec, int tile, int split_k, bo
         case 13:
             if (!vec) return launch_tile<128, 128, 4, 2, 4, 3, 2, 2>(p, vec, split_k, stream);
             return launch_tile<96, 128, 1, 4, 4, 3, 2, 2>(p, vec, split_k, stream);
+        case 14:
+            if (!vec) return launch_tile<64, 64, 2, 2, 4, 3, 2, 2>(p, vec, split_k, stream);
+            return launch_tile<32, 32, 2, 2, 4, 3, 2, 2, 16, 2>(p, vec, split_k, stream);
         default: return launch_tile<256, 128, 4, 2, 4, 3, 2, 2>(p, vec, split_k, stream);
     }
 }

@@ -39,24 +39,31 @@ namespace {
 // LDS cycle per 16 lanes.)  The host guarantees that no tile needs more than PMAX
 // positions.
 //
-// Four consumer wavefronts (one per SIMD) own 32 tile rows x 64 channels each;
-// four producers issue the transfers.  Patch buffers alternate per channel
+// Four consumer wavefronts (one per SIMD) own a quarter of the tile rows each, times all
+// channels; four (two) producers issue the transfers.  Patch buffers alternate per channel
 // block, weight stages form a ring of three.  A producer's transfers complete
 // in issue order, which the waits below rely on: within a step the pieces of
 // the next patch are issued before the weights of step t+2, so waiting for the
 // weights of step t also covers every patch piece issued earlier.
 // ---------------------------------------------------------------------------
 // STAMP: the instance that records wall-clock stamps of its first workgroups (gpulet_conv2d_timeline).
-template <int BN, int NPROD, bool STAMP = false>
+//
+// Tiles (kPatchTiles below): 128 pixels x 64 channels is bound by the matrix pipeline and by LDS
+// and wants as many workgroups as CUs.  Launches with fewer workgroups wait for the ~50 B/clk at
+// which one CU takes transfers, so smaller tiles - 64 pixels x 32 or 16 channels, fewer patch
+// positions where the map allows it - spread the same layer over two to eight times as many CUs.
+// A consumer then owns 16 rows and uses the 16x16x32 matrix instruction.
+template <int BM, int BN, int PMAX, int NPROD, bool STAMP = false>
 __global__ __launch_bounds__((4 + NPROD) * 64) void conv3x3_patch_kernel(const ConvParams p) {
-    constexpr int BM = PATCH_BM, NCONS = 4, NS = 3, PMAX = PATCH_PMAX;
-    constexpr int NT = BN / 32;                    // MFMA tiles per consumer (one row of them)
+    constexpr int NCONS = 4, NS = 3, MF = BM / NCONS;
+    typedef Mma<MF> MM;
+    constexpr int NT = BN / MF;                    // MFMA tiles per consumer (one row of them)
     constexpr int PATCH = PMAX * BK;               // elements per patch buffer
     constexpr int BSTAGE = 3 * BN * BK;            // elements per weight stage: the three taps of a filter row
     constexpr int POPS = PMAX / 8 / NPROD;         // patch transfers per producer lane and channel block
     constexpr int BOPS = 3 * BN / 8 / NPROD;       // weight transfers per producer lane and step
     constexpr int RG = BN / 8;                     // groups of 8 rows per weight tile
-    static_assert(POPS % 2 == 0 && (3 * BN / 8) % NPROD == 0 && BN % 32 == 0, "transfer split");
+    static_assert(POPS % 2 == 0 && (3 * BN / 8) % NPROD == 0 && BN % MF == 0, "transfer split");
     static_assert(POPS / 2 + 2 * BOPS <= 63, "6-bit transfer counter");
     constexpr int LDT = BN + 8;
     constexpr int MAIN = 2 * PATCH + NS * BSTAGE;
@@ -71,7 +78,7 @@ __global__ __launch_bounds__((4 + NPROD) * 64) void conv3x3_patch_kernel(const C
     // weights, instead of every producer lane locating eight (which kept the first patch
     // transfer waiting for 0.9 us on a 10 us kernel).
     __shared__ unsigned ptab[PMAX];
-    static_assert(PMAX == NCONS * 64, "one table entry per consumer thread");
+    static_assert(PMAX <= NCONS * 64, "one table entry per consumer thread");
     __bf16 *const patch = lds;
     __bf16 *const wring = lds + 2 * PATCH;
 
@@ -108,7 +115,7 @@ __global__ __launch_bounds__((4 + NPROD) * 64) void conv3x3_patch_kernel(const C
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
-    f32x16 acc[NT];  // consumers only
+    typename MM::Acc acc[NT];  // consumers only
 
     if (wave >= NCONS) {
         // ------------------------------------------------------------ producer
@@ -183,7 +190,7 @@ __global__ __launch_bounds__((4 + NPROD) * 64) void conv3x3_patch_kernel(const C
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     } else {
         // ------------------------------------------------------------ consumer
-        const int frow = lane & 31, fhalf = lane >> 5;
+        const int frow = lane & (MF - 1), fpart = lane / MF;
         {
             // this thread's entry of the position table
             const int pos = wave * 64 + lane;
@@ -196,7 +203,7 @@ __global__ __launch_bounds__((4 + NPROD) * 64) void conv3x3_patch_kernel(const C
                 if (n < p.N && (unsigned)h < (unsigned)p.H && (unsigned)w < (unsigned)p.W)
                     e = static_cast<unsigned>((((n * p.H + h) * p.W + w) * p.C) * 2);
             }
-            ptab[pos] = e | static_cast<unsigned>(patch_key(pos, vr) << 4);
+            if (pos < PMAX) ptab[pos] = e | static_cast<unsigned>(patch_key(pos, vr) << 4);
         }
         __syncthreads();   // the table is complete (the producers wait here too)
         bias_regs = load_bias<BN, (NCONS + NPROD) * 64>(p, n0);
@@ -204,22 +211,22 @@ __global__ __launch_bounds__((4 + NPROD) * 64) void conv3x3_patch_kernel(const C
 #pragma unroll
         for (int j = 0; j < NT; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+            for (int v = 0; v < MM::NV; ++v) acc[j][v] = 0.f;
 
         // Patch position of this lane's tile row at tap (0, 0), and that position's patch row.
         int base = 0, brow = 0;
         {
-            const int l = l0 + wave * 32 + frow;
+            const int l = l0 + wave * MF + frow;
             const int rho = fdiv(l, p.d_tw);
             if (rho < NP) {
                 brow = vrow(rho) - v0;
                 base = brow * pwt + (l - rho * p.tw);
             }
         }
-        // A ring step is 12 depth steps of 16 (three taps x four).  The fragments of depth
+        // A ring step is 12 (6) depth steps of 16 (32): three taps x 64 channels.  The fragments of depth
         // step i+AHEAD are requested before the matrix instructions of step i are issued, so
         // LDS reads and matrix instructions overlap inside the one wavefront a SIMD runs.
-        constexpr int KSTEPS = 3 * (BK / 16), AHEAD = 2;
+        constexpr int KS = BK / MM::KSTEP, CPS = MM::KSTEP / CHUNK, KSTEPS = 3 * KS, AHEAD = 2;
         struct Frags {
             bf16x8 a, b[NT];
         };
@@ -231,14 +238,14 @@ __global__ __launch_bounds__((4 + NPROD) * 64) void conv3x3_patch_kernel(const C
                 if (r == 0 && blk == 0) st.at(3);   // the first patch and weights have landed
                 const __bf16 *wb = wring + r * BSTAGE;
                 auto load = [&](Frags &f, int i) {
-                    const int s = i / (BK / 16), ks = i % (BK / 16);
+                    const int s = i / KS, ks = i % KS;
                     const int pos = base + r * pwt + s;
                     f.a = *reinterpret_cast<const bf16x8 *>(pa + pos * BK +
-                                                            (((ks * 2 + fhalf) ^ patch_key(pos, brow + r)) * CHUNK));
+                                                            (((ks * CPS + fpart) ^ patch_key(pos, brow + r)) * CHUNK));
 #pragma unroll
                     for (int j = 0; j < NT; ++j)
                         f.b[j] = *reinterpret_cast<const bf16x8 *>(
-                            &wb[s * BN * BK + lds_pos(j * 32 + frow, ks * 2 + fhalf)]);
+                            &wb[s * BN * BK + lds_pos(j * MF + frow, ks * CPS + fpart)]);
                 };
                 Frags f[KSTEPS];
 #pragma unroll
@@ -249,7 +256,7 @@ __global__ __launch_bounds__((4 + NPROD) * 64) void conv3x3_patch_kernel(const C
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int j = 0; j < NT; ++j)
-                        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i].a, f[i].b[j], acc[j], 0, 0, 0);
+                        acc[j] = MM::mul(f[i].a, f[i].b[j], acc[j]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -261,14 +268,11 @@ __global__ __launch_bounds__((4 + NPROD) * 64) void conv3x3_patch_kernel(const C
     st.at(4);          // end of the main loop
     __syncthreads();
     if (wave < NCONS) {
-        const int frow = lane & 31, fhalf = lane >> 5;
 #pragma unroll
         for (int j = 0; j < NT; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = wave * 32 + 8 * (v >> 2) + 4 * fhalf + (v & 3);
-                stg[row * LDT + j * 32 + frow] = acc[j][v];
-            }
+            for (int v = 0; v < MM::NV; ++v)
+                stg[(wave * MF + MM::row(v, lane)) * LDT + j * MF + (lane & (MF - 1))] = acc[j][v];
     }
     __syncthreads();
     st.at(5);          // the tile is staged
@@ -554,44 +558,82 @@ __global__ __launch_bounds__(512) void conv3x3_c64_kernel(const ConvParams p, co
     }
 }
 
-// Column-block width for the patch kernel and whether every tile's patch fits PATCH_PMAX
-// positions.  Small images use the whole row (tiles then cross rows and images), wide ones
-// 16-pixel blocks (tiles are 8 x 16 rectangles) or 14-pixel blocks when that divides the row.
-bool patch_geometry(const ConvParams &p, int *tw_out) {
-    int tw;
-    if (p.Q <= 16) tw = p.Q;
-    else if (p.Q % 16 == 0) tw = 16;
-    else if (p.Q % 14 == 0) tw = 14;
-    else tw = 16;
-    const int NP = p.N * p.P, Hp = p.H + 2 * p.pad;
+// Column-block width for the patch kernel: small images use the whole row (tiles then cross rows
+// and images), wide ones 16-pixel blocks (tiles are 8 x 16 rectangles) or 14-pixel blocks when
+// that divides the row.
+int patch_width(const ConvParams &p) {
+    if (p.Q <= 16 || p.Q % 16 == 0) return std::min(p.Q, 16);
+    return p.Q % 14 == 0 ? 14 : 16;
+}
+
+// The largest patch, in positions, of any tile of bm pixels in column blocks of tw; stops counting
+// past `limit`.  Tiles start at multiples of bm in a sequence of images of P*tw pixels each, so
+// their phases repeat after lcm(bm, P*tw) pixels.
+int patch_positions(const ConvParams &p, int tw, int bm, int limit) {
+    const int NP = p.N * p.P, Hp = p.H + 2 * p.pad, image = p.P * tw;
     const long long lin = 1LL * NP * tw;
+    int a = image, b = bm;
+    while (b) { const int t = a % b; a = b; b = t; }
+    const long long end = std::min(lin, 1LL * (image / a) * bm);
     int worst = 0;
-    for (long long l0 = 0; l0 < lin; l0 += PATCH_BM) {
+    for (long long l0 = 0; l0 < end && worst <= limit; l0 += bm) {
         const int r0 = static_cast<int>(l0 / tw);
-        const int r1 = static_cast<int>(std::min<long long>(NP - 1, (l0 + PATCH_BM - 1) / tw));
+        const int r1 = static_cast<int>(std::min<long long>(NP - 1, (l0 + bm - 1) / tw));
         const int v0 = (r0 / p.P) * Hp + r0 % p.P, v1 = (r1 / p.P) * Hp + r1 % p.P + 2;
         worst = std::max(worst, (v1 - v0 + 1) * (tw + 2));
-        if (worst > PATCH_PMAX) return false;
     }
-    *tw_out = tw;
-    return true;
+    return worst;
+}
+
+// The patch kernel's tiles.  us_block: measured time of a 64-channel block on one CU.
+struct PatchTile {
+    int bm, bn, pmax;
+    double us_block;
+};
+const PatchTile kPatchTiles[] = {{128, 64, PATCH_PMAX, 1.35}, {64, 32, 192, 0.60}, {64, 32, 128, 0.52}, {64, 16, 192, 0.45}, {64, 16, 128, 0.36}};
+
+template <int BM, int BN, int PMAX, bool STAMP = false>
+void launch_patch_tile(const ConvParams &p, hipStream_t stream) {
+    constexpr int NPROD = BN >= 32 ? 4 : 2;   // 16 filters x 3 taps make too few transfers for four producers
+    hipLaunchKernelGGL((conv3x3_patch_kernel<BM, BN, PMAX, NPROD, STAMP>), dim3(static_cast<unsigned>(p.tiles_per_xcd * 8)),
+                       dim3((4 + NPROD) * 64), 0, stream, p);
+}
+
+long long patch_tiles(const ConvParams &p, int tw, const PatchTile &t) {
+    return ((1LL * p.N * p.P * tw + t.bm - 1) / t.bm) * ((p.Q + tw - 1) / tw) * ((p.K + t.bn - 1) / t.bn);
 }
 
 }  // namespace
 
 bool patch_eligible(const ConvParams &p, bool vec, int *tw_out) {
+    *tw_out = patch_width(p);
     return vec && p.ldx == p.C && p.R == 3 && p.S == 3 && p.stride == 1 && p.pad == 1 && p.C % BK == 0 && p.P == p.H &&
-           p.Q == p.W && patch_geometry(p, tw_out);
+           p.Q == p.W && patch_positions(p, *tw_out, PATCH_BM, PATCH_PMAX) <= PATCH_PMAX;
 }
 
-hipError_t launch_patch(ConvParams p, int tw, hipStream_t stream) {
-    constexpr int BN = 64;
+// The tile to run on n_cu CUs: among those whose workgroups are all resident at once the one with the
+// shortest block of 64 channels, else 128x64.  (A second round of a small tile costs more than the
+// one round of the larger: 512 -> 512 on 7x7 at batch 32 20.5 us in 400 workgroups of 64x32, 16.4 in
+// 100 of 128x64.)  *one_round: whether the workgroups of the 128x64 tile are resident at once.
+int patch_variant(const ConvParams &p, int tw, int n_cu, bool *one_round) {
+    // Workgroups are dealt round-robin to 8 dies and, inside a die, to 4 shader engines; a CU takes
+    // one workgroup, so every shader engine must have a CU for each of its share.
+    int best = 0;
+    for (int i = 0; i < static_cast<int>(sizeof(kPatchTiles) / sizeof(kPatchTiles[0])); ++i) {
+        const PatchTile &t = kPatchTiles[i];
+        const bool resident = ((patch_tiles(p, tw, t) + 7) / 8 + 3) / 4 <= n_cu / 32;
+        if (i == 0 && one_round) *one_round = resident;
+        if (resident && t.us_block < kPatchTiles[best].us_block && patch_positions(p, tw, t.bm, t.pmax) <= t.pmax) best = i;
+    }
+    return best;
+}
+
+hipError_t launch_patch(ConvParams p, int tw, int variant, hipStream_t stream) {
+    const PatchTile &t = kPatchTiles[variant];
     p.tw = tw;
     p.n_cb = (p.Q + tw - 1) / tw;
-    const long long lin = 1LL * p.N * p.P * tw;
-    const int tiles_m = static_cast<int>((lin + PATCH_BM - 1) / PATCH_BM) * p.n_cb;
-    p.tiles_n = (p.K + BN - 1) / BN;
-    p.n_tiles = tiles_m * p.tiles_n;
+    p.tiles_n = (p.K + t.bn - 1) / t.bn;
+    p.n_tiles = static_cast<int>(patch_tiles(p, tw, t));
     p.split_k = 1;
     p.tiles_per_xcd = (p.n_tiles + 7) / 8;
     p.d_tiles_n = make_fastdiv(p.tiles_n);
@@ -599,12 +641,17 @@ hipError_t launch_patch(ConvParams p, int tw, hipStream_t stream) {
     p.d_ncb = make_fastdiv(p.n_cb);
     p.d_pwt = make_fastdiv(tw + 2);
     p.d_hp = make_fastdiv(p.H + 2 * p.pad);
-    if (p.stamps)
-        hipLaunchKernelGGL((conv3x3_patch_kernel<BN, 4, true>), dim3(static_cast<unsigned>(p.tiles_per_xcd * 8)),
-                           dim3(8 * 64), 0, stream, p);
-    else
-        hipLaunchKernelGGL((conv3x3_patch_kernel<BN, 4>), dim3(static_cast<unsigned>(p.tiles_per_xcd * 8)),
-                           dim3(8 * 64), 0, stream, p);
+    switch (variant) {
+        case 1: launch_patch_tile<64, 32, 192>(p, stream); break;
+        case 2: launch_patch_tile<64, 32, 128>(p, stream); break;
+        case 3: launch_patch_tile<64, 16, 192>(p, stream); break;
+        case 4: launch_patch_tile<64, 16, 128>(p, stream); break;
+        default:
+            if (p.stamps)
+                launch_patch_tile<128, 64, PATCH_PMAX, true>(p, stream);
+            else
+                launch_patch_tile<128, 64, PATCH_PMAX>(p, stream);
+    }
     return hipGetLastError();
 }
 

@@ -88,6 +88,48 @@ def test_conv_patch_kernel_parity(part, case):
     assert np.all(got[:, :8] == -512.0) and np.all(got[:, 8 + K:] == -512.0)
 
 
+# N, C, H, W, K: few enough 3x3 workgroups that the automatic choice takes the small patch tiles
+SMALL_PATCH_CASES = [
+    (1, 128, 7, 7, 40),        # 64 x 16, short patch; 49 of 64 rows, ragged third filter tile
+    (1, 64, 14, 14, 24),       # 64 x 16, the patch of a full tile is exactly 128 positions
+    (3, 64, 7, 7, 72),         # 64 x 16, long patch: a tile spans images
+    (5, 256, 14, 14, 264),     # 64 x 32, long patch
+    (1, 64, 28, 28, 520),      # 64 x 32, short patch, two column blocks
+    (1, 192, 5, 3, 8),         # smaller than one tile
+]
+
+
+@pytest.mark.parametrize("case", SMALL_PATCH_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_conv_small_patch_tiles_parity(part, case):
+    N, C, H, W, K = case
+    x, w, b = conv_tensors(19, N, C, H, W, K, 3)
+    res = inputs.tensor(19, "res_small_patch", (N, K, H, W), "normal")
+    got, raw = gpu_conv(part, x, w, b, 1, 1, True, residual=res)
+    assert_conv_close(got, x, w, b, 1, 1, True, residual=res)
+    for tile in (7, 14):                       # same sums as the large patch tile and the gathering kernel
+        assert torch.equal(raw, gpu_conv(part, x, w, b, 1, 1, True, residual=res, tile=tile)[1]), tile
+
+
+# N, C, H, W, K, R, S, stride, pad: depth orders of the gathering kernel at their limits
+DEPTH_ORDER_CASES = [
+    (1, 64, 9, 9, 16, 7, 7, 1, 3),     # 49 taps: more than a mask of taps holds
+    (2, 64, 8, 8, 24, 1, 31, 1, 15),   # 31 taps in one filter row: the widest mask
+    (1, 128, 6, 5, 40, 5, 5, 2, 2),    # two channel blocks, most taps outside the image
+    (2, 72, 7, 9, 40, 1, 1, 2, 0),     # 1x1 with 8 of 64 channels in the last slice
+]
+
+
+@pytest.mark.parametrize("case", DEPTH_ORDER_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_conv_depth_orders_parity(part, case):
+    N, C, H, W, K, R, S, stride, pad = case
+    x, w, b = conv_tensors(21, N, C, H, W, K, R, S)
+    ref = oracle.conv2d(x, w, b, stride, pad, relu=True)
+    mag = conv_mag(x, w, b, stride, pad)
+    for tile in (0, 2, 3, 14):
+        got, _ = gpu_conv(part, x, w, b, stride, pad, True, tile=tile)
+        assert_close(got, ref, mag, what=tile)
+
+
 # N, C, H, W, K: 3x3, stride 1, pad 1, C a multiple of 64 -> the tall tile (a pixel rectangle of one image
 # with its input patch in LDS, weights streamed tap by tap; tile 11)
 TALL_CASES = [
