@@ -35,6 +35,12 @@ __device__ __forceinline__ int fdiv(int n, const FastDiv f) {
     return static_cast<int>((static_cast<unsigned long long>(static_cast<unsigned>(n)) * f.mul) >> f.shift);
 }
 
+// Workgroups are dealt round-robin to the eight dies, each with its own L2.  The index of the
+// piece of work that gives every die a contiguous run of `per_die` pieces, in a grid of 8 * per_die
+// workgroups; `bid` counts from a multiple of 8.
+__device__ __forceinline__ int die_block(int per_die, int bid) { return (bid & 7) * per_die + (bid >> 3); }
+__device__ __forceinline__ int die_block(int per_die) { return die_block(per_die, blockIdx.x); }
+
 // Two floats -> two bf16 (round to nearest even) in one dword, the first in the low half.
 __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
     const f32x2 v = {lo, hi};

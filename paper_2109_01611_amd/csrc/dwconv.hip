@@ -25,7 +25,9 @@ struct DwParams {
     int N, C, H, W, R, S, stride, pad, relu, P, Q;
     int qt;     // thread columns per output row = ceil(Q / TQ)
     int total;  // work items
-    FastDiv d_cv, d_qt, d_p;  // 3x3 kernel: divisions by C/8, qt and P
+    int p_tiles;         // 3x3 kernels: thread rows per image
+    int blocks_per_die;  // 3x3 kernels: workgroups per die (die_block)
+    FastDiv d_cv, d_qt, d_p;  // 3x3 kernels: divisions by the channel groups, qt and p_tiles
 };
 
 __device__ __forceinline__ void unpack8(const uint4 &v, float f[8]) {
@@ -35,6 +37,13 @@ __device__ __forceinline__ void unpack8(const uint4 &v, float f[8]) {
         f[2 * i] = __uint_as_float(u[i] << 16);
         f[2 * i + 1] = __uint_as_float(u[i] & 0xFFFF0000u);
     }
+}
+
+__device__ __forceinline__ void unpack4(const uint2 &v, float f[4]) {
+    f[0] = __uint_as_float(v.x << 16);
+    f[1] = __uint_as_float(v.x & 0xFFFF0000u);
+    f[2] = __uint_as_float(v.y << 16);
+    f[3] = __uint_as_float(v.y & 0xFFFF0000u);
 }
 
 __device__ __forceinline__ unsigned short bf16_bits(float f) {
@@ -114,18 +123,24 @@ __global__ __launch_bounds__(256) void dwconv_vec8(const DwParams p) {
 
 // 3x3 filters (every depthwise layer of MobileNet): the generic kernel above walks rows and
 // columns in loops with tests, so each of its 18 loads waits for the previous one's use, and a
-// layer of 24 MB took 20 us.  Here the taps are unrolled at compile time and every input load
-// (buffer loads: an offset pushed out of range returns zero, so padding needs no branch) and
-// every filter load is issued before the first multiply-add.  Same work split (8 channels x TQ
-// adjacent pixels per thread) and the same summation order, so the bits are those of the kernel
-// above.
+// layer of 24 MB took 20 us.  In the two kernels below the taps are unrolled at compile time and
+// every input load (buffer loads: an offset pushed out of range returns zero, so padding needs no
+// branch) and every filter load is issued before the first multiply-add.  Same summation order
+// (bias, then filter rows and columns ascending), so the bits are those of the kernel above.  Both
+// give every die a contiguous run of work items (die_block): neighbouring output rows share input
+// rows, and dealt round-robin over the dies each of these was fetched into two or three L2s
+// (batch 32: 128 channels 75x75 stride 2 13.0 -> 10.2 us, 512 channels 19x19 9.3 -> 8.8).
+//
+// Stride 2: 8 channels x TQ adjacent pixels of one output row per thread.
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4_t;
+typedef __attribute__((ext_vector_type(2))) unsigned u32x2_t;
 
-template <int STRIDE, int TQ>
-__global__ __launch_bounds__(256) void dwconv3x3_vec8(const DwParams p, const unsigned x_bytes) {
+template <int TQ>
+__global__ __launch_bounds__(256) void dwconv3x3_s2(const DwParams p, const unsigned x_bytes) {
+    constexpr int STRIDE = 2;
     constexpr int SPAN = (TQ - 1) * STRIDE + 3;  // input columns the TQ pixels touch
     constexpr unsigned OOB = 0x80000000u;
-    const int idx = blockIdx.x * 256 + threadIdx.x;
+    const int idx = die_block(p.blocks_per_die) * 256 + threadIdx.x;
     if (idx >= p.total) return;
     const int cv = p.C >> 3;
     int t = fdiv(idx, p.d_cv);
@@ -201,6 +216,95 @@ __global__ __launch_bounds__(256) void dwconv3x3_vec8(const DwParams p, const un
     }
 }
 
+// Stride 1: 4 channels of TQ x TP = 4 x 2 output pixels per thread.  With 8 channels of 4 x 1 pixels
+// (the stride-2 kernel's split) a thread held 192 registers, two wavefronts per SIMD, and every input
+// element was loaded 4.5 times and unpacked as often: the layer waited for issue and L1, not for memory.
+// Half the channels leave room for a second output row (3 loads per element, 126 registers, four wavefronts):
+// batch 32, 32 channels 150x150 (92 MB) 32.2 -> 28.1 us, 128 on 75x75 32.2 -> 27.5, 256 on 38x38 17.5 -> 13.2,
+// 512 on 19x19 10.5 -> 9.3.  Smaller tiles load more (4 x 1 10.2 us on 19x19), 4 x 4 wants more registers
+// (256 on 38x38 14.5 us); a rolling walk down the rows has too few wavefronts (44 us and more on 75x75), and
+// at stride 2, where rows are shared less, two rows gain nothing (13.0 and 12.8 us).
+template <int TQ, int TP>
+__global__ __launch_bounds__(256) void dwconv3x3_tile(const DwParams p, const unsigned x_bytes) {
+    constexpr int SPAN = TQ + 2, ROWS = TP + 2;   // input columns and rows of the tile
+    constexpr unsigned OOB = 0x80000000u;
+    const int idx = die_block(p.blocks_per_die) * 256 + threadIdx.x;
+    if (idx >= p.total) return;
+    const int cv = p.C >> 2;
+    const int t = fdiv(idx, p.d_cv);
+    const int c = (idx - t * cv) * 4;
+    const int t1 = fdiv(t, p.d_qt);
+    const int q0 = (t - t1 * p.qt) * TQ;
+    const int n = fdiv(t1, p.d_p);
+    const int p0 = (t1 - n * p.p_tiles) * TP;
+    const int h0 = p0 - p.pad, w_first = q0 - p.pad;
+
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16 *>(p.x), 0, x_bytes, 0x00020000);
+    u32x2_t xr[ROWS][SPAN];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+        const bool h_ok = static_cast<unsigned>(h0 + i) < static_cast<unsigned>(p.H);
+        const int row = (((n * p.H + h0 + i) * p.W + w_first) * p.C + c) * 2;
+#pragma unroll
+        for (int u = 0; u < SPAN; ++u) {
+            const bool ok = h_ok && static_cast<unsigned>(w_first + u) < static_cast<unsigned>(p.W);
+            xr[i][u] = __builtin_amdgcn_raw_buffer_load_b64(rx, ok ? static_cast<unsigned>(row + u * (p.C * 2)) : OOB, 0, 0);
+        }
+    }
+    uint2 wr[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) wr[k] = *reinterpret_cast<const uint2 *>(p.w + k * p.C + c);
+    float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (p.b) bias = *reinterpret_cast<const float4 *>(p.b + c);
+    float wt[9][4];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) unpack4(wr[k], wt[k]);
+    float acc[TP][TQ][4];
+#pragma unroll
+    for (int o = 0; o < TP; ++o)
+#pragma unroll
+        for (int j = 0; j < TQ; ++j) {
+            acc[o][j][0] = bias.x;
+            acc[o][j][1] = bias.y;
+            acc[o][j][2] = bias.z;
+            acc[o][j][3] = bias.w;
+        }
+    const unsigned limit = relu_limit(p.relu);
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+#pragma unroll
+        for (int u = 0; u < SPAN; ++u) {
+            float xv[4];
+            unpack4(make_uint2(xr[i][u][0], xr[i][u][1]), xv);
+#pragma unroll
+            for (int o = 0; o < TP; ++o) {
+                const int r = i - o;
+                if (r < 0 || r >= 3) continue;
+#pragma unroll
+                for (int j = 0; j < TQ; ++j) {
+                    const int sx = u - j;  // input column u is tap sx of pixel j
+                    if (sx < 0 || sx >= 3) continue;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[o][j][e] = fmaf(xv[e], wt[r * 3 + sx][e], acc[o][j][e]);
+                }
+            }
+        }
+        if (i >= 2) {
+            const int o = i - 2;
+            if (p0 + o < p.P) {
+                __bf16 *y = p.y + (((n * p.P + p0 + o) * p.Q + q0) * p.C + c);
+#pragma unroll
+                for (int j = 0; j < TQ; ++j) {
+                    if (q0 + j >= p.Q) break;
+                    *reinterpret_cast<uint2 *>(y + j * p.C) =
+                        make_uint2(relu_or_pass(pack_bf16(acc[o][j][0], acc[o][j][1]), limit),
+                                   relu_or_pass(pack_bf16(acc[o][j][2], acc[o][j][3]), limit));
+                }
+            }
+        }
+    }
+}
+
 // Any channel count or alignment: one thread per output element.
 __global__ __launch_bounds__(256) void dwconv_scalar(const DwParams p) {
     const int idx = blockIdx.x * 256 + threadIdx.x;
@@ -252,20 +356,19 @@ hipError_t launch_dwconv(const void *x, const void *w, const float *b, void *y, 
                      reinterpret_cast<uintptr_t>(b) % 16 == 0;
     if (vec && R == 3 && S == 3 && (stride == 1 || stride == 2)) {
         const unsigned x_bytes = static_cast<unsigned>(2LL * N * H * W * C);
-        p.d_cv = make_fastdiv(C / 8);
-        p.d_p = make_fastdiv(P);
-        p.d_qt = make_fastdiv((Q + (stride == 1 ? 4 : 2) - 1) / (stride == 1 ? 4 : 2));
-        if (stride == 1) {
-            constexpr int TQ = 4;
-            p.qt = (Q + TQ - 1) / TQ;
-            p.total = N * P * p.qt * (C / 8);
-            hipLaunchKernelGGL((dwconv3x3_vec8<1, TQ>), dim3((p.total + 255) / 256), dim3(256), 0, stream, p, x_bytes);
-        } else {
-            constexpr int TQ = 2;
-            p.qt = (Q + TQ - 1) / TQ;
-            p.total = N * P * p.qt * (C / 8);
-            hipLaunchKernelGGL((dwconv3x3_vec8<2, TQ>), dim3((p.total + 255) / 256), dim3(256), 0, stream, p, x_bytes);
-        }
+        const int tq = stride == 1 ? 4 : 2, cv = C / (stride == 1 ? 4 : 8);
+        p.qt = (Q + tq - 1) / tq;
+        p.p_tiles = stride == 1 ? (P + 1) / 2 : P;
+        p.total = N * p.p_tiles * p.qt * cv;
+        p.d_cv = make_fastdiv(cv);
+        p.d_qt = make_fastdiv(p.qt);
+        p.d_p = make_fastdiv(p.p_tiles);
+        p.blocks_per_die = (p.total + 8 * 256 - 1) / (8 * 256);
+        const dim3 grid(static_cast<unsigned>(8 * p.blocks_per_die));
+        if (stride == 1)
+            hipLaunchKernelGGL((dwconv3x3_tile<4, 2>), grid, dim3(256), 0, stream, p, x_bytes);
+        else
+            hipLaunchKernelGGL(dwconv3x3_s2<2>, grid, dim3(256), 0, stream, p, x_bytes);
     } else if (vec) {
         constexpr int TQ = 4;
         p.qt = (Q + TQ - 1) / TQ;

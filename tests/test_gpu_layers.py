@@ -680,6 +680,16 @@ def test_depthwise_conv_parity(part, case):
         assert not np.any(got == -512.0)
 
 
+# 3x3, N, C, H, W, stride, pad: odd and single output rows against tiles of two, ragged tiles of four columns,
+# fewer work items than a workgroup and more than one run per die, padding wider than the tile
+@pytest.mark.parametrize("case", [(1, 8, 1, 1, 1, 1), (2, 40, 5, 7, 1, 1), (3, 16, 6, 4, 1, 0), (1, 24, 2, 13, 1, 2),
+                                  (5, 72, 19, 18, 1, 1), (5, 72, 19, 18, 2, 1), (1, 8, 2, 3, 2, 1)],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_depthwise_3x3_tiles(part, case):
+    N, C, H, W, stride, pad = case
+    test_depthwise_conv_parity(part, (N, C, H, W, 3, stride, pad))
+
+
 def test_depthwise_argument_errors(part):
     t = torch.zeros(64, dtype=torch.bfloat16, device=DEV)
     for bad in [dict(N=0), dict(C=0), dict(k=0), dict(stride=0), dict(pad=-1), dict(H=2, k=5)]:
