@@ -52,7 +52,10 @@ namespace {
 // and wants as many workgroups as CUs.  Launches with fewer workgroups wait for the ~50 B/clk at
 // which one CU takes transfers, so smaller tiles - 64 pixels x 32 or 16 channels, fewer patch
 // positions where the map allows it - spread the same layer over two to eight times as many CUs.
-// A consumer then owns 16 rows and uses the 16x16x32 matrix instruction.
+// A consumer then owns 16 rows and uses the 16x16x32 matrix instruction.  128 x 32 serves the launches
+// in between, too many 64-pixel tiles and half the CUs idle with 128 x 64: the same fragment reads
+// per row and half the weights (256 -> 256, 14x14, batch 8 on 128 CUs 9.6 -> 7.2 us; ResNet-50 batch 8 on
+// half the GPU 499 -> 489 us, batch 32 790 -> 783).
 template <int BM, int BN, int PMAX, int NPROD, bool STAMP = false>
 __global__ __launch_bounds__((4 + NPROD) * 64) void conv3x3_patch_kernel(const ConvParams p) {
     constexpr int NCONS = 4, NS = 3, MF = BM / NCONS;
@@ -590,7 +593,8 @@ struct PatchTile {
     int bm, bn, pmax;
     double us_block;
 };
-const PatchTile kPatchTiles[] = {{128, 64, PATCH_PMAX, 1.35}, {64, 32, 192, 0.60}, {64, 32, 128, 0.52}, {64, 16, 192, 0.45}, {64, 16, 128, 0.36}};
+const PatchTile kPatchTiles[] = {{128, 64, PATCH_PMAX, 1.35}, {64, 32, 192, 0.60}, {64, 32, 128, 0.52}, {64, 16, 192, 0.45}, {64, 16, 128, 0.36},
+                                 {128, 32, PATCH_PMAX, 1.00}};
 
 template <int BM, int BN, int PMAX, bool STAMP = false>
 void launch_patch_tile(const ConvParams &p, hipStream_t stream) {
@@ -646,6 +650,7 @@ hipError_t launch_patch(ConvParams p, int tw, int variant, hipStream_t stream) {
         case 2: launch_patch_tile<64, 32, 128>(p, stream); break;
         case 3: launch_patch_tile<64, 16, 192>(p, stream); break;
         case 4: launch_patch_tile<64, 16, 128>(p, stream); break;
+        case 5: launch_patch_tile<128, 32, PATCH_PMAX>(p, stream); break;
         default:
             if (p.stamps)
                 launch_patch_tile<128, 64, PATCH_PMAX, true>(p, stream);

@@ -110,6 +110,12 @@ def test_conv_small_patch_tiles_parity(part, case):
         assert torch.equal(raw, gpu_conv(part, x, w, b, 1, 1, True, residual=res, tile=tile)[1]), tile
 
 
+# too many workgroups of 64 x 32, few enough of 128 x 32: a ragged last filter tile, tiles that span images
+@pytest.mark.parametrize("case", [(8, 64, 14, 14, 520), (40, 128, 7, 7, 392)], ids=lambda c: "x".join(map(str, c)))
+def test_conv_patch_tile_of_32_filters_parity(part, case):
+    test_conv_small_patch_tiles_parity(part, case)
+
+
 # N, C, H, W, K, R, S, stride, pad: depth orders of the gathering kernel at their limits
 DEPTH_ORDER_CASES = [
     (1, 64, 9, 9, 16, 7, 7, 1, 3),     # 49 taps: more than a mask of taps holds
