@@ -5,6 +5,7 @@
 // (1x1 with a short depth), conv_stem.hip (at most four input channels) and
 // conv_pooled.hip (max pool fused into a 1x1 convolution); conv_common.h holds
 // what they share.
+#include <algorithm>
 #include <atomic>
 
 #include "conv_common.h"
@@ -324,7 +325,7 @@ bool conv_pool2_fusable(const ConvArgs &a, const LaunchCtx &ctx) {
 // Independent layers in one launch.  Every member must be a layer the gathering kernel would
 // run anyway, unsplit: 16-byte gathers, no fused pool, one output, and none of the specialised
 // kernels chosen for its shape; otherwise the members are launched one after the other.  The
-// tile shared by all members minimises the work on the busiest CU over the members' tiles
+// tile shared by all members minimises the slices on the busiest CU over the members' tiles
 // together.  Results are those of separate launches, bit for bit.
 hipError_t launch_conv_group(const ConvArgs *a, int n, const LaunchCtx &ctx, hipStream_t stream, int *launches) {
     ConvParams p[MAX_GROUP];
@@ -354,17 +355,27 @@ hipError_t launch_conv_group(const ConvArgs *a, int n, const LaunchCtx &ctx, hip
         tiles128 += tj;
         slices128 += tj * ((p[j].Kg + BK - 1) / BK);
     }
+    // The deepest member first: its workgroups start first, and a CU's second one is then a shallower one.
+    std::stable_sort(p, p + n, [](const ConvParams &a, const ConvParams &b) { return a.Kg > b.Kg; });
     int best = 0;
     double best_cost = 0.0;
     for (int o = 0; o < kNumTiles; ++o) {
         const TileChoice &t = kTiles[o];
-        long long tiles = 0;
-        for (int j = 0; j < n; ++j) tiles += 1LL * ((p[j].M + t.bm - 1) / t.bm) * ((p[j].K + t.bn - 1) / t.bn);
+        // Slices on the busiest CU, the one that takes workgroups 0, n_cu, 2 n_cu, ...: with members of
+        // different depths a round costs what its deepest workgroup costs (inception 5a at batch 32 on
+        // 128 CUs: 125 workgroups of 1440 deep and 100 of 832 and 800 in 64x64 tiles take 10.5 us, one round of
+        // 64x128 13.2; 4d at batch 1 on 64 CUs 7.2 us in 32x32, 8.7 in 64x64).
+        long long tiles = 0, slices = 0;
+        for (int j = 0; j < n; ++j) {
+            const long long first = (tiles + n_cu - 1) / n_cu;   // this member's first round
+            tiles += 1LL * ((p[j].M + t.bm - 1) / t.bm) * ((p[j].K + t.bn - 1) / t.bn);
+            slices += ((tiles + n_cu - 1) / n_cu - first) * ((p[j].Kg + BK - 1) / BK);
+        }
         double eff = t.eff;
         // the same bonus as in a single launch for 128x128 with two workgroups per CU, at the
         // members' mean depth (inception 3a's group at batch 32: 18.0 -> 15.8 us)
         if (t.id == 0 && tiles128 > n_cu) eff = std::min(1.2, 0.90 + 3.0 * tiles128 / slices128);
-        const double cost = static_cast<double>((tiles + n_cu - 1) / n_cu) * t.bm * t.bn / eff;
+        const double cost = static_cast<double>(slices) * t.bm * t.bn / eff;
         if (o == 0 || cost < best_cost) {
             best = t.id;
             best_cost = cost;

@@ -464,6 +464,15 @@ def test_independent_convs_in_one_launch(part, case):
             assert bool((cat[..., :8] == -512.0).all())
 
 
+# shallow members in front of deep ones, several rounds of the smallest tile: the launch reorders them
+@pytest.mark.parametrize("case", [(9, 14, 14, 96, [(0, 32, 40, 1, 1, 0, True), (0, 96, 136, 3, 1, 1, False), (32, 64, 72, 5, 1, 2, True)]),
+                                  (2, 9, 7, 64, [(0, 8, 8, 1, 1, 0, True), (0, 64, 8, 1, 1, 0, True), (0, 64, 40, 1, 2, 0, False),
+                                                 (0, 64, 24, 3, 1, 1, True)])],
+                         ids=lambda c: "x".join(map(str, c[:4])))
+def test_group_members_of_ascending_depth(part, case):
+    test_independent_convs_in_one_launch(part, case)
+
+
 # N, H, W, K: 3x3, stride 1, pad 1, exactly 64 input channels -> weights resident in registers (tile 10)
 C64_CASES = [
     (3, 14, 14, 64),        # whole rows per block; M = 588: ragged last tile, fewer tiles than workgroups
