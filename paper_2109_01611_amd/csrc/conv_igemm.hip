@@ -199,14 +199,15 @@ __device__ __forceinline__ void conv_igemm_body(const ConvParams &p, const int b
             i32x4 rx, rw;
         };
         // Walks the depth.  next(slice) works out the transfers of the next slice and advances the
-        // depth position; slices past the end of the depth transfer zeros: they change no sum, or
-        // nobody reads them.  Step j waits for this lane's transfers of stage j (those of the NS-2
-        // later stages may stay in flight), meets everybody, and refills the LDS stage j-1 was read
-        // from with stage j+NS-1.  What it refills with is worked out in front of the barrier (the
-        // empty asm statements keep the compiler from moving it behind), so that the transfers
-        // follow the barrier at once; with two slices per barrier the consumers' reads of the stage
-        // want that time (3x3 512 -> 512, 14x14, stride 2, batch 1: 8.5 us so, 8.8 the other way).  The loop is not unrolled: a launch starts with cold instruction caches, and
-        // the producers' code has to be short.
+        // depth position; slices past the end of the workgroup's share transfer zeros: they change no
+        // sum (the second half of a stage of two slices), or nobody reads them.  Step j waits for
+        // this lane's transfers of stage j (those of the NS-2 later stages may stay in flight),
+        // meets everybody, and refills the LDS stage j-1 was read from with stage j+NS-1.  What it
+        // refills with is worked out in front of the barrier (the empty asm statements keep the
+        // compiler from moving it behind), so that the transfers follow the barrier at once; with
+        // two slices per barrier the consumers' reads of the stage want that time (3x3 512 -> 512,
+        // 14x14, stride 2, batch 1: 8.5 us so, 8.8 the other way).  The loop is not unrolled: a
+        // launch starts with cold instruction caches, and the producers' code has to be short.
         auto run = [&](auto &&next) {
             constexpr bool EARLY = SPB == 1;
             unsigned base = ring_lds + pw * 8 * (BK * 2);
@@ -268,10 +269,12 @@ __device__ __forceinline__ void conv_igemm_body(const ConvParams &p, const int b
         // 0.15 us per slice of a 32x32 tile on 3x3 512 -> 512, 14x14, stride 2, against 0.06 for 1x1).
         if (DEPTH == Depth::POINT) {
             const i32x4 rx = make_rsrc(p.x, p.x_bytes);
-            int left = p.C - k_first * BK, soff = k_first * BK * 2;   // k_first < nk_all
+            // Channels of this workgroup's slices: its share of a split depth ends before the layer's depth does.
+            int left = SPLIT ? min(p.C - k_first * BK, nk * BK) : p.C;
+            int soff = k_first * BK * 2;
             const int cc8 = cc * CHUNK;
             run([&](Slice &sl) {
-                // lanes past the last channel, and all lanes past the last slice, transfer zeros
+                // lanes past the last channel, and all lanes past this workgroup's last slice, transfer zeros
                 const unsigned past = cc8 < left ? 0u : OOB;
                 sl.rx = rx;
                 sl.rw = rw;

@@ -611,6 +611,30 @@ def test_conv_split_depth_parity_and_reproducibility(part, case):
     assert diff <= 2.0 ** -6 * max(1.0, runs[3].float().abs().max().item())
 
 
+# 1x1 layers whose shares of the depth hold an odd number of slices while the tile takes two slices per
+# barrier: nothing of the next share may be added.  N, C, H, W, K, stride, pad and the largest number of shares
+ODD_SHARE_CASES = [
+    (1, 832, 7, 7, 384, 1, 0, 2),      # 13 slices as 7 + 6
+    (1, 528, 14, 14, 256, 1, 0, 2),    # 9 slices as 5 + 4, the last a quarter full
+    (1, 2048, 7, 7, 512, 1, 0, 3),     # 32 as 11 + 11 + 10
+    (1, 2048, 7, 7, 512, 1, 0, 8),     # 32 as six shares of 5 and one of 2
+    (1, 1032, 13, 13, 72, 2, 0, 4),    # strided; 17 slices, the last an eighth full
+    (1, 832, 7, 7, 128, 1, 1, 2),      # padded: another walk of the depth
+]
+
+
+@pytest.mark.parametrize("case", ODD_SHARE_CASES, ids=lambda c: "x".join(map(str, c)))
+def test_conv_split_depth_with_odd_shares(part, case):
+    N, C, H, W, K, stride, pad, max_split = case
+    x, w, b = conv_tensors(22, N, C, H, W, K, 1)
+    gpulet.set_conv_split_k(max_split)
+    try:
+        got, _ = gpu_conv(part, x, w, b, stride, pad, True)
+    finally:
+        gpulet.set_conv_split_k(1)
+    assert_conv_close(got, x, w, b, stride, pad, True)
+
+
 def test_conv_is_deterministic(part):
     x, w, b = conv_tensors(12, 4, 64, 28, 28, 96, 3)
     _, r0 = gpu_conv(part, x, w, b, 1, 1, True)
