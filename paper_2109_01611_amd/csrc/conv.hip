@@ -108,7 +108,7 @@ hipError_t make_params(const ConvArgs &a, const LaunchCtx &ctx, ConvParams &p, b
     // up to the last channel the layer reads of the last pixel
     p.x_bytes = static_cast<unsigned>(2LL * ((1LL * a.N * a.H * a.W - 1) * p.ldx + a.C));
     p.w_bytes = static_cast<unsigned>(2LL * a.K * a.R * a.S * a.C);
-    p.tap_inner = (a.C % BK == 0 && a.R * a.S < 32) ? 1 : 0;   // conv_igemm keeps a bit per tap
+    p.tap_inner = a.C % BK == 0 ? 1 : 0;
     p.vec_store = (a.y_ch_stride % 8 == 0 && a.y_ch_offset % 8 == 0 && reinterpret_cast<uintptr_t>(a.y) % 16 == 0 &&
                    reinterpret_cast<uintptr_t>(a.b) % 16 == 0 &&
                    (!a.residual || (a.K % 8 == 0 && reinterpret_cast<uintptr_t>(a.residual) % 16 == 0)) &&

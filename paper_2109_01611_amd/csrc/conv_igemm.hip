@@ -295,36 +295,51 @@ __device__ __forceinline__ void conv_igemm_body(const ConvParams &p, const int b
             const int cb = k_first / rs;
             int t = k_first - cb * rs, r = fdiv(t, p.d_s), s = t - r * p.S, c2 = cb * BK * 2;
             int xo = (r * p.W + s) * p.ldx * 2 + c2, wo = t * p.C * 2 + c2, left = nk;
-            unsigned out[AINS];
-            taps_outside(out);
 #pragma unroll
             for (int i = 0; i < AINS; ++i) a_off[i] += cc * (CHUNK * 2);
-            run([&](Slice &sl) {
-                const bool ok = left > 0;
-                sl.rx = rx;
-                sl.rw = rw;
-                sl.rx[2] = ok ? static_cast<int>(x_size) : 0;   // past the last slice everything is out of range
-                sl.rw[2] = ok ? static_cast<int>(p.w_bytes) : 0;
-                sl.xs = ok ? xo : 0;
-                sl.ws = ok ? wo : 0;
+            // offset(i): the offset of this lane's pixel row i, with the OOB bit where the tap lies outside
+            auto walk = [&](auto &&offset) {
+                run([&](Slice &sl) {
+                    const bool ok = left > 0;
+                    sl.rx = rx;
+                    sl.rw = rw;
+                    sl.rx[2] = ok ? static_cast<int>(x_size) : 0;   // past the last slice everything is out of range
+                    sl.rw[2] = ok ? static_cast<int>(p.w_bytes) : 0;
+                    sl.xs = ok ? xo : 0;
+                    sl.ws = ok ? wo : 0;
 #pragma unroll
-                for (int i = 0; i < AINS; ++i) sl.a[i] = ((out[i] << (31 - t)) & OOB) | static_cast<unsigned>(a_off[i]);
+                    for (int i = 0; i < AINS; ++i) sl.a[i] = offset(i);
 #pragma unroll
-                for (int i = 0; i < BINS; ++i) sl.b[i] = b_off[i];
-                --left;
-                ++t;
-                wo += p.C * 2;
-                xo += p.ldx * 2;
-                if (++s == p.S) {
-                    s = 0;
-                    xo += (p.W - p.S) * p.ldx * 2;
-                    if (++r == p.R) {
-                        r = t = 0;
-                        c2 += BK * 2;
-                        xo = wo = c2;
+                    for (int i = 0; i < BINS; ++i) sl.b[i] = b_off[i];
+                    --left;
+                    ++t;
+                    wo += p.C * 2;
+                    xo += p.ldx * 2;
+                    if (++s == p.S) {
+                        s = 0;
+                        xo += (p.W - p.S) * p.ldx * 2;
+                        if (++r == p.R) {
+                            r = t = 0;
+                            c2 += BK * 2;
+                            xo = wo = c2;
+                        }
                     }
-                }
-            });
+                });
+            };
+            // The mask walk is laid out first (the other way round 3x3 512 -> 512, 14x14, stride 2, batch 1
+            // takes 9.3 us instead of 9.0).  7x7 64 -> 64 on 28x28 at batch 8 with both tests 10.2 us, in the
+            // order of the stored weights 11.0.
+            if (__builtin_expect(rs < 32, 1)) {
+                unsigned out[AINS];
+                taps_outside(out);
+                walk([&](int i) { return ((out[i] << (31 - t)) & OOB) | static_cast<unsigned>(a_off[i]); });
+            } else {
+                // more taps than a mask holds: both bounds tests for every tap
+                walk([&](int i) {
+                    const bool in = ((unsigned)(a_h0[i] + r) < (unsigned)p.H) & ((unsigned)(a_w0[i] + s) < (unsigned)p.W);
+                    return in ? static_cast<unsigned>(a_off[i]) : OOB;
+                });
+            }
         } else {
             // Depth position of the chunk this lane fetches next: element index g, its filter tap
             // (r, s), channel c, and the tap's byte offset inside the image.  With dense pixels

@@ -119,6 +119,7 @@ def test_conv_patch_tile_of_32_filters_parity(part, case):
 # N, C, H, W, K, R, S, stride, pad: depth orders of the gathering kernel at their limits
 DEPTH_ORDER_CASES = [
     (1, 64, 9, 9, 16, 7, 7, 1, 3),     # 49 taps: more than a mask of taps holds
+    (2, 128, 9, 11, 40, 4, 8, 2, 3),   # 32 taps: one more than a mask holds, two channel blocks
     (2, 64, 8, 8, 24, 1, 31, 1, 15),   # 31 taps in one filter row: the widest mask
     (1, 128, 6, 5, 40, 5, 5, 2, 2),    # two channel blocks, most taps outside the image
     (2, 72, 7, 9, 40, 1, 1, 2, 0),     # 1x1 with 8 of 64 channels in the last slice
@@ -134,6 +135,21 @@ def test_conv_depth_orders_parity(part, case):
     for tile in (0, 2, 3, 14):
         got, _ = gpu_conv(part, x, w, b, stride, pad, True, tile=tile)
         assert_close(got, ref, mag, what=tile)
+
+
+# Channel counts that are multiples of 64 add all taps of one block of 64 channels before the next block,
+# however large the filter: 2^30 - 2^30 from two taps of the first block, then 1 from the second.  In the
+# order of the stored weights the 1 would be absorbed in between.
+@pytest.mark.parametrize("filt", [(5, 5), (1, 31), (4, 8), (3, 11), (7, 7)], ids=lambda f: "x".join(map(str, f)))
+def test_conv_taps_of_a_channel_block_are_added_first(part, filt):
+    R, S = filt
+    x = np.zeros((1, 128, R, S))
+    w = np.zeros((8, 128, R, S))
+    x[0, 0, R - 1, 0] = x[0, 0, R - 1, 1] = x[0, 64, R - 1, 0] = 1.0
+    w[:, 0, R - 1, 0], w[:, 0, R - 1, 1], w[:, 64, R - 1, 0] = 2.0 ** 30, -2.0 ** 30, 1.0
+    for tile in (-1, 0, 1, 2, 3, 4, 5, 6, 12, 13, 14):
+        got, _ = gpu_conv(part, x, w, None, 1, 0, False, tile=tile)
+        assert np.all(got == 1.0), tile
 
 
 # N, C, H, W, K: 3x3, stride 1, pad 1, C a multiple of 64 -> the tall tile (a pixel rectangle of one image
