@@ -329,7 +329,8 @@ gpulet_status gpulet_maxpool3_conv1x1_fwd(const void *x, const void *w, const fl
  *   2 position table complete      3 first input patch and weights in LDS
  *   4 end of the main loop         5 fp32 tile staged in LDS
  *   6 output stores issued         7 unused (0)
- * (tiles 7 and 11 of gpulet_set_conv_tile).  The kernel that keeps the weights
+ * (tiles 7 and 11 of gpulet_set_conv_tile, and the smaller tiles of kernel 7 that
+ * the automatic choice takes for small launches).  The kernel that keeps the weights
  * of 64 input channels in registers (tile 10) walks over many pixel tiles and
  * records instead: 0 first instruction, 1 weights requested, and around its
  * fourth pixel tile 2 arrival at the "patch landed" barrier, 3 patch there,

@@ -596,11 +596,14 @@ struct PatchTile {
 const PatchTile kPatchTiles[] = {{128, 64, PATCH_PMAX, 1.35}, {64, 32, 192, 0.60}, {64, 32, 128, 0.52}, {64, 16, 192, 0.45}, {64, 16, 128, 0.36},
                                  {128, 32, PATCH_PMAX, 1.00}};
 
-template <int BM, int BN, int PMAX, bool STAMP = false>
+template <int BM, int BN, int PMAX>
 void launch_patch_tile(const ConvParams &p, hipStream_t stream) {
     constexpr int NPROD = BN >= 32 ? 4 : 2;   // 16 filters x 3 taps make too few transfers for four producers
-    hipLaunchKernelGGL((conv3x3_patch_kernel<BM, BN, PMAX, NPROD, STAMP>), dim3(static_cast<unsigned>(p.tiles_per_xcd * 8)),
-                       dim3((4 + NPROD) * 64), 0, stream, p);
+    const dim3 grid(static_cast<unsigned>(p.tiles_per_xcd * 8)), block((4 + NPROD) * 64);
+    if (p.stamps)
+        hipLaunchKernelGGL((conv3x3_patch_kernel<BM, BN, PMAX, NPROD, true>), grid, block, 0, stream, p);
+    else
+        hipLaunchKernelGGL((conv3x3_patch_kernel<BM, BN, PMAX, NPROD>), grid, block, 0, stream, p);
 }
 
 long long patch_tiles(const ConvParams &p, int tw, const PatchTile &t) {
@@ -651,11 +654,7 @@ hipError_t launch_patch(ConvParams p, int tw, int variant, hipStream_t stream) {
         case 3: launch_patch_tile<64, 16, 192>(p, stream); break;
         case 4: launch_patch_tile<64, 16, 128>(p, stream); break;
         case 5: launch_patch_tile<128, 32, PATCH_PMAX>(p, stream); break;
-        default:
-            if (p.stamps)
-                launch_patch_tile<128, 64, PATCH_PMAX, true>(p, stream);
-            else
-                launch_patch_tile<128, 64, PATCH_PMAX>(p, stream);
+        default: launch_patch_tile<128, 64, PATCH_PMAX>(p, stream);
     }
     return hipGetLastError();
 }

@@ -892,6 +892,24 @@ def test_conv_timeline_records_ordered_stamps_for_the_patch_and_tall_kernels(par
     assert run(2, 64, 8, 8, 64, 1, 0, -1) == []           # a 1x1 layer runs a kernel that records nothing
 
 
+# the tiles that the automatic choice takes on 256 CUs: 64 x 16 (long and short patch), 64 x 32 (long and short), 128 x 32;
+# enough of them that the first workgroup of every die has one
+@pytest.mark.parametrize("case", [(2, 64, 14, 14, 128), (5, 64, 7, 7, 200), (5, 256, 14, 14, 264), (1, 64, 28, 28, 520),
+                                  (8, 64, 14, 14, 520)], ids=lambda c: "x".join(map(str, c)))
+def test_conv_timeline_records_stamps_for_the_small_patch_tiles(part, case):
+    N, C, H, W, K = case
+    x = torch.zeros((N, H, W, C), dtype=torch.bfloat16, device=DEV)
+    w = torch.zeros((K, 3, 3, C), dtype=torch.bfloat16, device=DEV)
+    y = torch.full((N, H, W, K), 3.0, dtype=torch.bfloat16, device=DEV)
+    torch.cuda.synchronize()
+    rows = gpulet.conv2d_timeline(x, w, None, y, N, C, H, W, K, 3, 3, 1, 1, True, stream=part.stream, warmup=3)
+    assert bool((y == 0).all())
+    assert len(rows) == 8
+    for r in rows:
+        assert r[7] == 0 and all(0 < a <= b for a, b in zip(r[:6], r[1:7])), r
+        assert r[6] - r[0] < 20000, r
+
+
 # N, In, Out
 FC_CASES = [(32, 400, 120), (32, 120, 84), (32, 84, 10), (1, 2048, 1000), (8, 1024, 1000),
             (33, 72, 17), (5, 8, 3), (40, 4096, 1000), (16, 25088, 64), (2, 100, 7),
