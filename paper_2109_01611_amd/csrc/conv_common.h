@@ -272,6 +272,9 @@ __device__ __forceinline__ void finish_tile(const ConvParams &p, const float *st
         const int c = threadIdx.x % BN, kc = n0 + c;
         if (kc >= p.K) return;
         const float bias1 = p.b ? p.b[kc] : 0.f;
+        // Waited for here: left pending, it makes the compiler guard its register in the 16-byte path
+        // below with a wait for all of memory in front of every residual load and every store.
+        asm volatile("" ::"v"(bias1));
         __bf16 *yb = p.y + p.y_off + kc;
         int ld = p.ldy;
         if (DUAL && kc >= p.k2) {
@@ -291,6 +294,10 @@ __device__ __forceinline__ void finish_tile(const ConvParams &p, const float *st
     const int cv = threadIdx.x % VPR, row0 = threadIdx.x / VPR;
     const int k = n0 + cv * 8;
     if (k >= p.K) return;
+    // Waited for once: the bias was requested before the main loop and has long arrived, but the compiler
+    // does not know that and would wait for it, and with it for the store before, in front of every store.
+    // (1x1 64 -> 256, 56x56, batch 32, 256x128 tiles: 23.2 us with both waits in the loop, 22.2 without.)
+    asm volatile("" ::"v"(br.lo.x), "v"(br.hi.x));
     {
         // a thread keeps its 8 channels, so it also keeps its destination
         __bf16 *yb = p.y + p.y_off + k;
