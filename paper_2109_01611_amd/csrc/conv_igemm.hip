@@ -198,44 +198,84 @@ __device__ __forceinline__ void conv_igemm_body(const ConvParams &p, const int b
             int xs, ws;
             i32x4 rx, rw;
         };
+        // Starts the transfers of a slice into the LDS stage `at` bytes behind `base`.
+        auto transfer = [&](const Slice &sl, unsigned base, const int at) {
+#pragma unroll
+            for (int i = 0; i < AINS; ++i) dma16(sl.rx, base, at + i * PROWS * (BK * 2), sl.a[i], sl.xs);
+#pragma unroll
+            for (int i = 0; i < BINS; ++i) dma16(sl.rw, base, at + (BM + i * PROWS) * (BK * 2), sl.b[i], sl.ws);
+        };
+        // Keeps the compiler from moving the computation of a slice behind the next barrier.
+        auto settle = [&](Slice &sl) {
+            asm volatile("" : "+s"(sl.xs), "+s"(sl.ws));
+#pragma unroll
+            for (int i = 0; i < AINS; ++i) asm volatile("" : "+v"(sl.a[i]));
+        };
         // Walks the depth.  next(slice) works out the transfers of the next slice and advances the
         // depth position; slices past the end of the workgroup's share transfer zeros: they change no
         // sum (the second half of a stage of two slices), or nobody reads them.  Step j waits for
         // this lane's transfers of stage j (those of the NS-2 later stages may stay in flight),
         // meets everybody, and refills the LDS stage j-1 was read from with stage j+NS-1.  What it
-        // refills with is worked out in front of the barrier (the empty asm statements keep the
-        // compiler from moving it behind), so that the transfers follow the barrier at once; with
-        // two slices per barrier the consumers' reads of the stage want that time (3x3 512 -> 512,
-        // 14x14, stride 2, batch 1: 8.5 us so, 8.8 the other way).  The loop is not unrolled: a
-        // launch starts with cold instruction caches, and the producers' code has to be short.
+        // refills with is worked out in front of the barrier, so that the transfers follow the
+        // barrier at once; with two slices per barrier the consumers' reads of the stage want that
+        // time (3x3 512 -> 512, 14x14, stride 2, batch 1: 8.5 us so, 8.8 the other way).
+        //
+        // Up to six transfers per lane and slice the loop is not unrolled: such tiles serve small
+        // launches, which start with cold instruction caches and want short code.  From seven on
+        // (128x128, 256x128, 192x128, 96x128, 128x32, 32x128) the producers' instructions count,
+        // and the ring position is a compile-time constant in an unrolled body.  Rolled and unrolled:
+        // 1x1 64 -> 256, 56x56, batch 32 in 96x128 26.0 and 25.6 us, in 128x128 17.1 and 17.0; 3x3
+        // 256 -> 256, 56x56, batch 4 on 96 CUs in 96x128 37.9 and 37.6; 1x1 480 -> 24, 14x14, batch 32 in
+        // 128x32 4.6 and 4.4; 1x1 1024 -> 256, 7x7, batch 5 in 32x128 5.4 and 5.0.
         auto run = [&](auto &&next) {
-            constexpr bool EARLY = SPB == 1;
             unsigned base = ring_lds + pw * 8 * (BK * 2);
-            const unsigned end = base + NS * STAGE * 2;
             Slice sl;
-            if (EARLY) next(sl);
-#pragma unroll 1
-            for (int j = 1 - NS; j < nst; ++j) {
-                if (EARLY) {
-                    asm volatile("" : "+s"(sl.xs), "+s"(sl.ws), "+s"(base));
-#pragma unroll
-                    for (int i = 0; i < AINS; ++i) asm volatile("" : "+v"(sl.a[i]));
-                }
-                if (j >= 0) {
-                    __builtin_amdgcn_s_waitcnt(vmcnt_imm((AINS + BINS) * SPB * (NS - 2)));
+            if constexpr (AINS + BINS >= 7) {
+                static_assert(SPB == 1, "the unrolled walk takes one slice per stage");
+                auto issue = [&](int stage) {
+                    transfer(sl, base, stage * STAGE * 2);
+                    next(sl);
+                };
+                auto step = [&](int refill) {
+                    settle(sl);
+                    __builtin_amdgcn_s_waitcnt(vmcnt_imm((AINS + BINS) * (NS - 2)));
                     __syncthreads();
+                    issue(refill);
+                };
+                next(sl);
+#pragma unroll
+                for (int i = 0; i < NS - 1; ++i) issue(i);
+                int kt = 0;
+                for (; kt + NS <= nst; kt += NS) {
+#pragma unroll
+                    for (int u = 0; u < NS; ++u) step((u + NS - 1) % NS);
                 }
 #pragma unroll
-                for (int h = 0; h < SPB; ++h) {
-                    if (!EARLY) next(sl);
+                for (int u = 0; u < NS - 1; ++u)
+                    if (kt + u < nst) step((u + NS - 1) % NS);
+            } else {
+                constexpr bool EARLY = SPB == 1;
+                const unsigned end = base + NS * STAGE * 2;
+                if (EARLY) next(sl);
+#pragma unroll 1
+                for (int j = 1 - NS; j < nst; ++j) {
+                    if (EARLY) {
+                        settle(sl);
+                        asm volatile("" : "+s"(base));
+                    }
+                    if (j >= 0) {
+                        __builtin_amdgcn_s_waitcnt(vmcnt_imm((AINS + BINS) * SPB * (NS - 2)));
+                        __syncthreads();
+                    }
 #pragma unroll
-                    for (int i = 0; i < AINS; ++i) dma16(sl.rx, base, h * SLICE * 2 + i * PROWS * (BK * 2), sl.a[i], sl.xs);
-#pragma unroll
-                    for (int i = 0; i < BINS; ++i) dma16(sl.rw, base, h * SLICE * 2 + (BM + i * PROWS) * (BK * 2), sl.b[i], sl.ws);
-                    if (EARLY) next(sl);
+                    for (int h = 0; h < SPB; ++h) {
+                        if (!EARLY) next(sl);
+                        transfer(sl, base, h * SLICE * 2);
+                        if (EARLY) next(sl);
+                    }
+                    base += STAGE * 2;
+                    if (base == end) base -= NS * STAGE * 2;
                 }
-                base += STAGE * 2;
-                if (base == end) base -= NS * STAGE * 2;
             }
         };
 
