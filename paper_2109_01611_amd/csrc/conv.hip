@@ -325,8 +325,8 @@ bool conv_pool2_fusable(const ConvArgs &a, const LaunchCtx &ctx) {
 // Independent layers in one launch.  Every member must be a layer the gathering kernel would
 // run anyway, unsplit: 16-byte gathers, no fused pool, one output, and none of the specialised
 // kernels chosen for its shape; otherwise the members are launched one after the other.  The
-// tile shared by all members minimises the slices on the busiest CU over the members' tiles
-// together.  Results are those of separate launches, bit for bit.
+// tile shared by all members minimises the work of the busiest CU (slices and a fixed part per
+// round) over the members' tiles together.  Results are those of separate launches, bit for bit.
 hipError_t launch_conv_group(const ConvArgs *a, int n, const LaunchCtx &ctx, hipStream_t stream, int *launches) {
     ConvParams p[MAX_GROUP];
     bool together = n >= 2 && n <= MAX_GROUP;
@@ -361,10 +361,14 @@ hipError_t launch_conv_group(const ConvArgs *a, int n, const LaunchCtx &ctx, hip
     double best_cost = 0.0;
     for (int o = 0; o < kNumTiles; ++o) {
         const TileChoice &t = kTiles[o];
-        // Slices on the busiest CU, the one that takes workgroups 0, n_cu, 2 n_cu, ...: with members of
-        // different depths a round costs what its deepest workgroup costs (inception 5a at batch 32 on
-        // 128 CUs: 125 workgroups of 1440 deep and 100 of 832 and 800 in 64x64 tiles take 10.5 us, one round of
-        // 64x128 13.2; 4d at batch 1 on 64 CUs 7.2 us in 32x32, 8.7 in 64x64).
+        // Work of the busiest CU, the one that takes workgroups 0, n_cu, 2 n_cu, ...  With members of
+        // different depths a round costs the slices of its deepest workgroup (4d at batch 1 on 64
+        // CUs 7.1 us in 32x32, 7.6 in 64x64) and, whatever the depth, what fetching the arguments, the
+        // first transfers and the epilogue take: as much as 7 to 9 slices, fitted over every tile of
+        // 432 groups (inception blocks, ResNet shortcuts, detection heads; batch 1 to 32 on 64 to 256
+        // CUs).  Without that part a tile with a shallow second round looks too cheap (4a at batch 32 on
+        // 192 CUs: 196 tiles of 128x128 12.6 us, 294 of 128x64 12.0).
+        constexpr int kFixedSlices = 8;
         long long tiles = 0, slices = 0;
         for (int j = 0; j < n; ++j) {
             const long long first = (tiles + n_cu - 1) / n_cu;   // this member's first round
@@ -372,10 +376,12 @@ hipError_t launch_conv_group(const ConvArgs *a, int n, const LaunchCtx &ctx, hip
             slices += ((tiles + n_cu - 1) / n_cu - first) * ((p[j].Kg + BK - 1) / BK);
         }
         double eff = t.eff;
-        // the same bonus as in a single launch for 128x128 with two workgroups per CU, at the
-        // members' mean depth (inception 3a's group at batch 32: 18.0 -> 15.8 us)
-        if (t.id == 0 && tiles128 > n_cu) eff = std::min(1.2, 0.90 + 3.0 * tiles128 / slices128);
-        const double cost = static_cast<double>(slices) * t.bm * t.bn / eff;
+        // The same bonus as in a single launch for 128x128 with two workgroups per CU, at the
+        // members' mean depth (inception 3a's group at batch 32: 18.0 -> 15.8 us), but no more than
+        // 1.1: a second, shallower member fills less (3b at batch 32 on 256 CUs 30.4 us, 28.7 in 128x64).
+        if (t.id == 0 && tiles128 > n_cu) eff = std::min(1.1, 0.90 + 3.0 * tiles128 / slices128);
+        const long long rounds = (tiles + n_cu - 1) / n_cu;
+        const double cost = static_cast<double>(slices + kFixedSlices * rounds) * t.bm * t.bn / eff;
         if (o == 0 || cost < best_cost) {
             best = t.id;
             best_cost = cost;
