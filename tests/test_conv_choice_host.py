@@ -7,6 +7,7 @@ import subprocess
 
 import pytest
 
+import test_gpu_layers
 from paper_2109_01611_amd import build
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -64,3 +65,12 @@ def test_tile_of_a_launch_group(launches, case):
         assert (kernel, got) == ("group", tile)
         depth = {"%dx%dx%dx%dx%d" % l[:5]: l[1] * l[5] * l[6] for l in layers}
         assert [depth[m] for m in members] == sorted(depth.values(), reverse=True)      # deepest member first
+
+
+def test_the_small_patch_cases_reach_every_patch_tile(launches):
+    # the layers of the GPU parity tests, on a whole GPU: 1, 2 = 64x32 with a long and a short patch, 3, 4 = 64x16, 5 = 128x32
+    want = {(1, 128, 7, 7, 40): 4, (1, 64, 14, 14, 24): 4, (3, 64, 7, 7, 72): 4, (2, 64, 14, 14, 72): 3, (9, 128, 7, 7, 72): 3,
+            (5, 256, 14, 14, 264): 1, (1, 64, 28, 28, 520): 2, (1, 192, 5, 3, 8): 4, (8, 64, 14, 14, 520): 5, (40, 128, 7, 7, 392): 5}
+    assert set(test_gpu_layers.SMALL_PATCH_CASES) <= set(want)
+    got = launches([(256, [c + (3, 3, 1, 1, c[1])]) for c in want])
+    assert [g[0][:2] for g in got] == [("patch", v) for v in want.values()]

@@ -92,7 +92,9 @@ def test_conv_patch_kernel_parity(part, case):
 SMALL_PATCH_CASES = [
     (1, 128, 7, 7, 40),        # 64 x 16, short patch; 49 of 64 rows, ragged third filter tile
     (1, 64, 14, 14, 24),       # 64 x 16, the patch of a full tile is exactly 128 positions
-    (3, 64, 7, 7, 72),         # 64 x 16, long patch: a tile spans images
+    (3, 64, 7, 7, 72),         # 64 x 16, short patch (126 positions): a tile spans images
+    (2, 64, 14, 14, 72),       # 64 x 16, long patch (160 positions), ragged fifth filter tile
+    (9, 128, 7, 7, 72),        # 64 x 16, long patch (144 positions): a tile spans three images
     (5, 256, 14, 14, 264),     # 64 x 32, long patch
     (1, 64, 28, 28, 520),      # 64 x 32, short patch, two column blocks
     (1, 192, 5, 3, 8),         # smaller than one tile
