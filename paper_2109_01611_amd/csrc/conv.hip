@@ -147,9 +147,9 @@ hipError_t make_params(const ConvArgs &a, const LaunchCtx &ctx, ConvParams &p, b
     return hipSuccess;
 }
 
-// Which kernel runs a layer: 0..6 a gathering tile (with `split` workgroups per tile), 7 the
-// patch kernel (column block `tw`, tile `patch_tile`), 8 the streaming 1x1 kernel, 9 the stem kernel, 10 the
-// resident-weight kernel (column block `tw64`).
+// Which kernel runs a layer: 0..6 and 12..14 a gathering tile (with `split` workgroups per tile), 7
+// the patch kernel (column block `tw`, tile `patch_tile`), 8 the streaming 1x1 kernel, 9 the stem
+// kernel, 10 the resident-weight kernel (column block `tw64`), 11 the tall tile (`th11` x `tw11`).
 struct Choice {
     int best, split, tw, tw64, th11, tw11, patch_tile;
     double cost;   // of `best` in the cost model's units when it is a gathering tile or the tall tile, else 0

@@ -147,12 +147,9 @@ __device__ __forceinline__ int lds_pos(int row, int chunk) {
 // at a tap touch 16 different 16-byte bank groups.
 __device__ __forceinline__ int patch_key(int pos, int prow) { return ((pos - 2 * prow) >> 1) & 7; }
 
-// Workgroups are dealt round-robin to the eight dies, each with its own L2.
-// Give every die a contiguous run of tiles so that tiles sharing a pixel block
-// (all their channel tiles) hit the same L2.
-__device__ __forceinline__ int tile_of_block(const ConvParams &p, int bid) {
-    return (bid & 7) * p.tiles_per_xcd + (bid >> 3);
-}
+// Every die gets a contiguous run of tiles, so that tiles sharing a pixel block (all their
+// channel tiles) hit the same L2.
+__device__ __forceinline__ int tile_of_block(const ConvParams &p, int bid) { return die_block(p.tiles_per_xcd, bid); }
 __device__ __forceinline__ int tile_of_block(const ConvParams &p) { return tile_of_block(p, blockIdx.x); }
 
 typedef __attribute__((ext_vector_type(4))) int i32x4;
@@ -365,7 +362,7 @@ constexpr int PATCH_PMAX = 256;
 // `vec` = C % 8 == 0 with 16-byte aligned x and w.
 // ---------------------------------------------------------------------------
 
-// conv_igemm.hip: gathering tiles 0..6 of gpulet_set_conv_tile (scalar-gather variant when !vec).
+// conv_igemm.hip: gathering tiles 0..6 and 12..14 of gpulet_set_conv_tile (scalar-gather variant when !vec).
 // `two_stage` selects the 64 KB ring of tile 0 (two workgroups per CU).
 hipError_t launch_igemm(const ConvParams &p, bool vec, int tile, int split_k, bool two_stage, hipStream_t stream);
 // n (2..MAX_GROUP) layers, all with 16-byte gathers, one tile shape, no depth split, one launch.

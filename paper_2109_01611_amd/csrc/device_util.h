@@ -39,7 +39,6 @@ __device__ __forceinline__ int fdiv(int n, const FastDiv f) {
 // piece of work that gives every die a contiguous run of `per_die` pieces, in a grid of 8 * per_die
 // workgroups; `bid` counts from a multiple of 8.
 __device__ __forceinline__ int die_block(int per_die, int bid) { return (bid & 7) * per_die + (bid >> 3); }
-__device__ __forceinline__ int die_block(int per_die) { return die_block(per_die, blockIdx.x); }
 
 // Two floats -> two bf16 (round to nearest even) in one dword, the first in the low half.
 __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {

@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256) void dwconv3x3_s2(const DwParams p, const unsi
     constexpr int STRIDE = 2;
     constexpr int SPAN = (TQ - 1) * STRIDE + 3;  // input columns the TQ pixels touch
     constexpr unsigned OOB = 0x80000000u;
-    const int idx = die_block(p.blocks_per_die) * 256 + threadIdx.x;
+    const int idx = die_block(p.blocks_per_die, blockIdx.x) * 256 + threadIdx.x;
     if (idx >= p.total) return;
     const int cv = p.C >> 3;
     int t = fdiv(idx, p.d_cv);
@@ -228,7 +228,7 @@ template <int TQ, int TP>
 __global__ __launch_bounds__(256) void dwconv3x3_tile(const DwParams p, const unsigned x_bytes) {
     constexpr int SPAN = TQ + 2, ROWS = TP + 2;   // input columns and rows of the tile
     constexpr unsigned OOB = 0x80000000u;
-    const int idx = die_block(p.blocks_per_die) * 256 + threadIdx.x;
+    const int idx = die_block(p.blocks_per_die, blockIdx.x) * 256 + threadIdx.x;
     if (idx >= p.total) return;
     const int cv = p.C >> 2;
     const int t = fdiv(idx, p.d_cv);
