@@ -7,6 +7,7 @@ import subprocess
 
 import pytest
 
+import bench
 import test_gpu_layers
 from paper_2109_01611_amd import build
 
@@ -74,3 +75,13 @@ def test_the_small_patch_cases_reach_every_patch_tile(launches):
     assert set(test_gpu_layers.SMALL_PATCH_CASES) <= set(want)
     got = launches([(256, [c + (3, 3, 1, 1, c[1])]) for c in want])
     assert [g[0][:2] for g in got] == [("patch", v) for v in want.values()]
+
+
+def test_the_benchmark_names_the_kernel_it_times(launches):
+    # variant 0 is the 128x64 patch tile; its mangled name is in the library
+    assert launches([(256, [(32, 256, 14, 14, 256, 3, 3, 1, 1, 256)])])[0] == [("patch", 0, ["32x256x14x14x256"])]
+    name, args = bench.BENCH_KERNEL.rstrip(">").split("<")
+    mangled = "%d%sI%sE" % (len(name), name, "".join("Lb%dE" % (a == "true") if a in ("true", "false") else "Li%sE" % a
+                                                        for a in args.split(",")))
+    with open(build.LIB, "rb") as fh:
+        assert mangled.encode() in fh.read()
