@@ -299,7 +299,10 @@ gpulet_status gpulet_conv3x3_maxpool2_fwd(const void *x, const void *w, const fl
  * in its epilogue when its column blocks are a power of two wide) or has at
  * least 128 input channels and the tall-tile kernel, which pools in its
  * epilogue, costs the layer at most 15 % more than the kernel it would run
- * otherwise; the layer's own output buffer is then left unwritten.  Results are
+ * otherwise; the layer's own output buffer is then left unwritten.  The same
+ * switch governs runs of small layers (convolutions, max pools, fully connected
+ * layers whose tensors of one image fit in LDS together, as LeNet-5's), which go
+ * out as one launch that still writes every tensor.  Results are
  * bit-identical either way.  Process-wide.
  */
 gpulet_status gpulet_set_conv_pool_fusion(int on);

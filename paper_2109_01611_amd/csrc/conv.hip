@@ -308,7 +308,7 @@ hipError_t launch_conv(const ConvArgs &a, const LaunchCtx &ctx, hipStream_t stre
 // 15 % more than the kernel the layer would get by itself.  Layers that a specialised kernel takes
 // (all workgroups of the patch kernel resident, 64 input channels) keep it and their pool kernel.
 bool conv_pool2_fusable(const ConvArgs &a, const LaunchCtx &ctx) {
-    if (!g_pool_fusion.load() || g_tile_override.load() >= 0) return false;
+    if (!conv_fusion_allowed()) return false;
     if (a.pre_pool || a.y2 || a.pool_y || a.residual || !a.relu) return false;
     ConvParams p;
     bool vec = false;
@@ -392,6 +392,8 @@ hipError_t launch_conv_group(const ConvArgs *a, int n, const LaunchCtx &ctx, hip
 }
 
 void set_conv_split_k(int max_split) { g_max_split_k.store(max_split); }
+
+bool conv_fusion_allowed() { return g_pool_fusion.load() && g_tile_override.load() < 0; }
 
 void set_conv_pool_fusion(int on) { g_pool_fusion.store(on ? 1 : 0); }
 

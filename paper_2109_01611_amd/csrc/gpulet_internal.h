@@ -112,6 +112,8 @@ hipError_t launch_conv(const ConvArgs &a, const LaunchCtx &ctx, hipStream_t stre
 // layer alone (the tall tile, from 128 channels on).  `a.y` is the pooled destination.
 bool conv_pool2_fusable(const ConvArgs &a, const LaunchCtx &ctx);
 void set_conv_pool_fusion(int on);
+// Whether layers of different kinds may share a launch: not while pool fusion is switched off or a tile is forced.
+bool conv_fusion_allowed();
 // n independent layers (no member reads or overwrites what another writes), in one launch where
 // the kernels allow it.
 // *launches (if not null) receives the number of kernel launches made: 1 or n.
@@ -129,6 +131,23 @@ hipError_t launch_fc_static(const void *x, const void *w, const float *b, void *
                             int relu, int out_fp32, int n_cu, hipStream_t stream, bool *too_large);
 hipError_t launch_dwconv(const void *x, const void *w, const float *b, void *y, int N, int C, int H, int W,
                          int R, int S, int stride, int pad, int relu, int P, int Q, hipStream_t stream);
+
+// image_chain.hip: consecutive small layers, each reading what the one before wrote, as one launch with one
+// workgroup per image.  Every layer takes (C, H, W) to (K, P, Q) per image: convolutions with dense input and
+// output, max pools (R x R windows, K = C), fully connected layers (K outputs, P = Q = 1).  `y` is where the
+// layer's output goes for the whole batch, or null if nobody wants it in memory.
+constexpr int kMaxChain = 8;
+struct ChainLayer {
+    int kind;   // GPULET_OP_CONV, GPULET_OP_POOL (max), GPULET_OP_FC
+    int C, H, W, K, P, Q, R, S, stride, pad, relu, out_fp32;
+    const void *w;
+    const float *b;
+    void *y;
+};
+// Whether l[0 .. n) can run so (n >= 2); x and the destinations of convolutions and pools are 16-byte aligned.
+bool image_chain_applicable(const ChainLayer *l, int n);
+hipError_t launch_image_chain(const ChainLayer *l, int n, const void *x, int N, hipStream_t stream);
+
 hipError_t launch_probe(uint32_t *out, int n_blocks, hipStream_t stream);
 // blocks x waves wavefronts of nothing but 32x32x16 bf16 matrix instructions, 64 * iters each; out: one float
 // per thread.  dense: pseudo-random operands in (-1, 1) instead of zeros.

@@ -43,6 +43,7 @@ struct Step {
     bool record;            // a later layer on another lane waits for this one
     bool pool_next;         // CONV: the next layer is a 2x2 / stride 2 max pool that is the only reader of
                             // this layer's output; the pair may run as one launch (conv_pool2_fusable)
+    int chain_len;          // layers from this one on that may run as one launch with a workgroup per image (else 0)
 };
 
 struct Plan {
@@ -139,6 +140,49 @@ void assign_lanes(Plan &plan, int n_bufs, int n_lanes) {
     }
 }
 
+// What the launch of small layers needs to know of a step (activation pointers excepted);
+// false when the layer is not of a kind it takes.
+bool chain_layer(const Step &s, ChainLayer &l) {
+    l = ChainLayer{};
+    l.kind = s.op;
+    l.w = s.w;
+    l.b = s.b;
+    if (s.op == GPULET_OP_CONV) {
+        const ConvArgs &a = s.conv;
+        if (s.group_len != 1 || s.slice || s.res_buf >= 0 || s.out2_buf >= 0 || s.pool_buf >= 0 || a.pre_pool ||
+            a.x_ch_stride != 0)
+            return false;
+        l.C = a.C; l.H = a.H; l.W = a.W; l.K = a.K; l.P = a.P; l.Q = a.Q; l.R = a.R; l.S = a.S;
+        l.stride = a.stride; l.pad = a.pad; l.relu = a.relu;
+    } else if (s.op == GPULET_OP_POOL) {
+        if (s.mode != GPULET_POOL_MAX) return false;
+        l.C = l.K = s.C; l.H = s.H; l.W = s.W; l.P = s.P; l.Q = s.Q; l.R = l.S = s.k; l.stride = s.stride; l.pad = s.pad;
+    } else if (s.op == GPULET_OP_FC) {
+        // the source's own shape: the tensor the step before left, or the model's input
+        l.C = s.In; l.H = l.W = l.P = l.Q = 1; l.K = s.Out; l.relu = s.relu; l.out_fp32 = s.out_fp32;
+    } else {
+        return false;
+    }
+    return true;
+}
+
+// Runs of layers that take one image after the other through LDS (image_chain.hip): each reads what the one
+// before wrote, and none writes the run's input, which other images may still have to read.
+void find_chains(Plan &plan) {
+    for (size_t i = 0; i < plan.steps.size();) {
+        ChainLayer l[kMaxChain];
+        int best = 0;
+        for (int n = 0; n < kMaxChain && i + n < plan.steps.size(); ++n) {
+            const Step &s = plan.steps[i + n];
+            if (n > 0 && (s.in_buf != plan.steps[i + n - 1].out_buf || s.out_buf == plan.steps[i].in_buf)) break;
+            if (!chain_layer(s, l[n])) break;
+            if (n > 0 && image_chain_applicable(l, n + 1)) best = n + 1;
+        }
+        plan.steps[i].chain_len = best;
+        i += best > 0 ? best : 1;
+    }
+}
+
 size_t round_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 // Shape inference and validation of a model description for `batch` images.
@@ -181,6 +225,7 @@ gpulet_status build_plan(const gpulet_model_desc *m, int batch, Plan &plan) {
         s.lane = 0;
         s.record = false;
         s.pool_next = false;
+        s.chain_len = 0;
         int oc = 0, oh = 0, ow = 0, oelem = 2;
         if (L.op == GPULET_OP_CONV) {
             // in_ch_total > 0: the layer reads L.C channels from in_ch_offset on of wider pixels
@@ -333,6 +378,7 @@ gpulet_status build_plan(const gpulet_model_desc *m, int batch, Plan &plan) {
         }
         c.pool_next = only_reader;
     }
+    find_chains(plan);
     assign_lanes(plan, m->n_bufs, g_model_lanes.load());
 
     plan.offset.assign(static_cast<size_t>(m->n_bufs), static_cast<size_t>(-1));
@@ -348,6 +394,7 @@ gpulet_status build_plan(const gpulet_model_desc *m, int batch, Plan &plan) {
 
 struct Bound {
     const Plan *plan;
+    int batch;
     const void *in;
     void *out;
     char *ws;
@@ -368,6 +415,24 @@ hipError_t pool_event(gpulet_partition *p, size_t idx, hipEvent_t *ev) {
     }
     *ev = p->events[idx];
     return hipSuccess;
+}
+
+// Whether the run of small layers that starts at step i goes out as one launch: all on one lane, nothing
+// waiting for or waited for by another.
+bool chain_allowed(const std::vector<Step> &steps, size_t i) {
+    if (!conv_fusion_allowed()) return false;
+    for (size_t k = 0; k < static_cast<size_t>(steps[i].chain_len); ++k) {
+        const Step &s = steps[i + k];
+        if (s.lane != steps[i].lane || s.record || (k > 0 && !s.wait.empty())) return false;
+    }
+    return true;
+}
+
+bool chain_aligned(const ChainLayer *l, size_t n, const void *x) {
+    if (reinterpret_cast<uintptr_t>(x) % 16 != 0) return false;
+    for (size_t k = 0; k < n; ++k)
+        if (l[k].kind != GPULET_OP_FC && reinterpret_cast<uintptr_t>(l[k].y) % 16 != 0) return false;
+    return true;
 }
 
 // Enqueues every layer of one batch on the gpu-let's lanes; no host synchronisation.  Lane 0
@@ -404,6 +469,25 @@ hipError_t enqueue(const Bound &bd, gpulet_partition *p) {
             e = pool_event(p, kMaxLanes + static_cast<size_t>(d), &ev);
             if (e == hipSuccess) e = hipStreamWaitEvent(stream, ev, 0);
             if (e != hipSuccess) return e;
+        }
+        if (s.chain_len > 0 && chain_allowed(steps, i)) {
+            ChainLayer l[kMaxChain];
+            const size_t n = static_cast<size_t>(s.chain_len);
+            for (size_t k = 0; k < n; ++k) {
+                const Step &sk = steps[i + k];
+                chain_layer(sk, l[k]);
+                // a tensor whose buffer a later layer of the run takes over is not stored
+                bool taken = false;
+                for (size_t t = k + 1; t < n; ++t) taken = taken || steps[i + t].out_buf == sk.out_buf;
+                l[k].y = taken ? nullptr : bd.ptr(sk.out_buf);
+            }
+            if (chain_aligned(l, n, bd.ptr(s.in_buf))) {
+                e = launch_image_chain(l, static_cast<int>(n), bd.ptr(s.in_buf), bd.batch, stream);
+                if (e != hipSuccess) return e;
+                p->kernels_enqueued.fetch_add(1);
+                i += n - 1;
+                continue;
+            }
         }
         // A launch group whose members all sit on this lane goes out as one launch, after the
         // waits of every member; otherwise its members are launched one by one as usual.
@@ -616,7 +700,7 @@ extern "C" gpulet_status gpulet_run_model(const gpulet_model_desc *m, int batch,
     if (st != GPULET_OK) return st;
     st = check_run_args(plan, in, out, workspace, workspace_bytes);
     if (st != GPULET_OK) return st;
-    const Bound bd{&plan, in, out, static_cast<char *>(workspace)};
+    const Bound bd{&plan, batch, in, out, static_cast<char *>(workspace)};
     if (latency_ms) {
         EventPair ev;
         GPULET_HIP(ev.create());
@@ -641,7 +725,7 @@ extern "C" gpulet_status gpulet_profile_model(const gpulet_model_desc *m, int ba
     if (st != GPULET_OK) return st;
     st = check_run_args(plan, in, out, workspace, workspace_bytes);
     if (st != GPULET_OK) return st;
-    const Bound bd{&plan, in, out, static_cast<char *>(workspace)};
+    const Bound bd{&plan, batch, in, out, static_cast<char *>(workspace)};
 
     for (int i = 0; i < warmup; ++i) {
         GPULET_HIP(enqueue(bd, p));
@@ -730,7 +814,7 @@ extern "C" gpulet_status gpulet_model_graph_create(const gpulet_model_desc *m, i
     if (st != GPULET_OK) return st;
     st = check_run_args(plan, in, out_buf, workspace, workspace_bytes);
     if (st != GPULET_OK) return st;
-    const Bound bd{&plan, in, out_buf, static_cast<char *>(workspace)};
+    const Bound bd{&plan, batch, in, out_buf, static_cast<char *>(workspace)};
     GPULET_HIP(hipStreamSynchronize(p->stream));
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -871,8 +955,8 @@ extern "C" gpulet_status gpulet_profile_corun(
     st = check_run_args(plan_b, in_b, out_b, ws_b, ws_b_bytes);
     if (st != GPULET_OK) return st;
 
-    CorunSide sa{&plan_a, Bound{&plan_a, in_a, out_a, static_cast<char *>(ws_a)}, pa, batch_a, warmup, cap_a, lat_a};
-    CorunSide sb{&plan_b, Bound{&plan_b, in_b, out_b, static_cast<char *>(ws_b)}, pb, batch_b, warmup, cap_b, lat_b};
+    CorunSide sa{&plan_a, Bound{&plan_a, batch_a, in_a, out_a, static_cast<char *>(ws_a)}, pa, batch_a, warmup, cap_a, lat_a};
+    CorunSide sb{&plan_b, Bound{&plan_b, batch_b, in_b, out_b, static_cast<char *>(ws_b)}, pb, batch_b, warmup, cap_b, lat_b};
     std::atomic<int> ready{0}, done_a{0}, done_b{0};
     std::thread ta(corun_thread, &sa, &ready, window_ms, &done_a, &done_b);
     std::thread tb(corun_thread, &sb, &ready, window_ms, &done_b, &done_a);
