@@ -251,14 +251,39 @@ __device__ __forceinline__ BiasRegs load_bias(const ConvParams &p, int n0) {
     return r;
 }
 
+// The items of a thread in finish_tile: 8 channels of tile rows threadIdx.x / VPR + i * RSTEP.
+template <int BM, int BN, int NTHR>
+struct TileItems {
+    static constexpr int VPR = BN / 8;            // 8-channel groups per tile row
+    static constexpr int RSTEP = NTHR / VPR;      // tile rows between two items of a thread
+    static constexpr int ITEMS = (BM + RSTEP - 1) / RSTEP;
+    static_assert(NTHR % VPR == 0, "a thread keeps its channel group");
+};
+
+// The residual of a thread's items, requested at the start of a kernel like the bias.  Costs
+// 4 registers per item for the whole main loop, so only small tiles do it.
+template <int BM, int BN, int NTHR, typename PixelOf>
+__device__ __forceinline__ void load_residual(const ConvParams &p, int n0, uint4 (&rr)[TileItems<BM, BN, NTHR>::ITEMS],
+                                              PixelOf pixel_of) {
+    typedef TileItems<BM, BN, NTHR> T;
+    const int k = n0 + (threadIdx.x % T::VPR) * 8;
+#pragma unroll
+    for (int i = 0; i < T::ITEMS; ++i) {
+        const int row = threadIdx.x / T::VPR + i * T::RSTEP;
+        const int m = row < BM ? pixel_of(row) : -1;
+        rr[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (p.res && p.vec_store && k + 8 <= p.K && m >= 0) rr[i] = *reinterpret_cast<const uint4 *>(p.res + (m * p.K + k));
+    }
+}
+
+// `early` (not null): the residual was loaded by load_residual.
 template <int BM, int BN, int NTHR, bool DUAL = false, typename PixelOf>
 __device__ __forceinline__ void finish_tile(const ConvParams &p, const float *stg, int n0, const BiasRegs &br,
-                                            PixelOf pixel_of) {
+                                            PixelOf pixel_of, const uint4 *early = nullptr) {
     constexpr int LDT = BN + 8;
-    constexpr int VPR = BN / 8;            // 8-channel groups per tile row
-    constexpr int RSTEP = NTHR / VPR;      // tile rows between two items of a thread
-    constexpr int ITEMS = (BM + RSTEP - 1) / RSTEP;
-    static_assert(NTHR % VPR == 0, "a thread keeps its channel group");
+    constexpr int VPR = TileItems<BM, BN, NTHR>::VPR;
+    constexpr int RSTEP = TileItems<BM, BN, NTHR>::RSTEP;
+    constexpr int ITEMS = TileItems<BM, BN, NTHR>::ITEMS;
     if (!(p.vec_store && p.K % 8 == 0)) {
         // Destinations that do not allow aligned 16-byte stores (channel counts such as the 546
         // of a detection head, odd channel offsets): one element per thread and pass, with the
@@ -311,9 +336,9 @@ __device__ __forceinline__ void finish_tile(const ConvParams &p, const float *st
         for (int i = 0; i < ITEMS; ++i) {
             const int row = row0 + i * RSTEP;
             m[i] = row < BM ? pixel_of(row) : -1;
-            rr[i] = make_uint4(0u, 0u, 0u, 0u);
+            rr[i] = early ? early[i] : make_uint4(0u, 0u, 0u, 0u);
         }
-        if (p.res) {
+        if (!early && p.res) {
 #pragma unroll
             for (int i = 0; i < ITEMS; ++i)
                 if (m[i] >= 0) rr[i] = *reinterpret_cast<const uint4 *>(p.res + (m[i] * p.K + k));

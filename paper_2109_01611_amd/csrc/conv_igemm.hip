@@ -142,6 +142,12 @@ __device__ __forceinline__ void conv_igemm_body(const ConvParams &p, const int b
     const int tm = fdiv(tile, p.d_tiles_n), tn = tile - tm * p.tiles_n;
     const int m0 = tm * BM, n0 = tn * BN;
     const BiasRegs bias_regs = load_bias<BN, (CWM * CWN + NPROD) * 64>(p, n0);
+    // Small tiles, and tiles of which a CU holds only one workgroup, request the residual now as well.
+    constexpr bool EARLY_RES = DEPTH == Depth::POINT && !EXTRA && !SPLIT &&
+                               (BM * BN <= 64 * 64 || waves_per_simd(BM, BN, NS, SPB, CWM * CWN + NPROD) == (CWM * CWN + NPROD) / 4);
+    auto pixel_of = [&](int row) { return m0 + row < p.M ? m0 + row : -1; };
+    uint4 early[TileItems<BM, BN, (CWM * CWN + NPROD) * 64>::ITEMS];
+    if constexpr (EARLY_RES) load_residual<BM, BN, (CWM * CWN + NPROD) * 64>(p, n0, early, pixel_of);
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -603,7 +609,7 @@ __device__ __forceinline__ void conv_igemm_body(const ConvParams &p, const int b
         }
         // each thread re-reads only what it wrote itself, in the same iteration order
     }
-    finish_tile<BM, BN, NTHR, EXTRA>(p, stg, n0, bias_regs, [&](int row) { return m0 + row < p.M ? m0 + row : -1; });
+    finish_tile<BM, BN, NTHR, EXTRA>(p, stg, n0, bias_regs, pixel_of, EARLY_RES ? early : nullptr);
 }
 
 template <int BM, int BN, int CWM, int CWN, int NPROD, int NS, Depth DEPTH, bool EXTRA, bool SPLIT, int MF, int SPB>
