@@ -298,7 +298,15 @@ hipError_t launch_conv(const ConvArgs &a, const LaunchCtx &ctx, hipStream_t stre
         case 7: return launch_patch(p, c.tw, c.patch_tile, stream);
         default: {
             const long long tiles128 = 1LL * ((p.M + 127) / 128) * ((p.K + 127) / 128);
-            return launch_igemm(p, vec, c.best, c.split, tiles128 > n_cu, stream);
+            // 16x16 tiles where they still all start at once: a CU takes operands that are in no nearby cache
+            // at about 60 KB/us, however many of them it has requested (a ring of 8 stages instead of 3 made 32x32
+            // tiles 2 % slower), so what counts is how many CUs share the operands' transfer.  1x1 2048 -> 512 on 7x7 at
+            // batch 1 4.6 us in 32x32, 3x3/2 512 -> 512 on 14x14 9.0 and 7.8, 3x3/2 256 -> 256 on 28x28 6.0 and 5.4;
+            // with a second workgroup on a CU they lose.
+            int tile = c.best;
+            const long long tiles16 = 1LL * ((p.M + 15) / 16) * ((p.K + 15) / 16);
+            if (tile == 14 && vec && c.split == 1 && g_tile_override.load() < 0 && tiles16 <= n_cu) tile = kTile16;
+            return launch_igemm(p, vec, tile, c.split, tiles128 > n_cu, stream);
         }
     }
 }

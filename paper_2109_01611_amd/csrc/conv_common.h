@@ -389,6 +389,7 @@ constexpr int PATCH_PMAX = 256;
 
 // conv_igemm.hip: gathering tiles 0..6 and 12..14 of gpulet_set_conv_tile (scalar-gather variant when !vec).
 // `two_stage` selects the 64 KB ring of tile 0 (two workgroups per CU).
+constexpr int kTile16 = 15;   // 16x16, chosen in place of 14 (not a tile of gpulet_set_conv_tile)
 hipError_t launch_igemm(const ConvParams &p, bool vec, int tile, int split_k, bool two_stage, hipStream_t stream);
 // n (2..MAX_GROUP) layers, all with 16-byte gathers, one tile shape, no depth split, one launch.
 hipError_t launch_igemm_group(const ConvParams *p, int n, int tile, bool two_stage, hipStream_t stream);

@@ -887,6 +887,7 @@ hipError_t launch_igemm(const ConvParams &p, bool vec, int tile, int split_k, bo
         case 14:
             if (!vec) return launch_tile<64, 64, 2, 2, 4, 3, 2, 2>(p, vec, split_k, stream);
             return launch_tile<32, 32, 2, 2, 4, 3, 2, 2, 16, 2>(p, vec, split_k, stream);
+        case kTile16: return launch_tile<16, 16, 1, 1, 2, 3, 2, 2, 16, 4>(p, vec, split_k, stream);
         default: return launch_tile<256, 128, 4, 2, 4, 3, 2, 2>(p, vec, split_k, stream);
     }
 }
