@@ -148,6 +148,18 @@ struct ChainLayer {
 bool image_chain_applicable(const ChainLayer *l, int n);
 hipError_t launch_image_chain(const ChainLayer *l, int n, const void *x, int N, hipStream_t stream);
 
+// conv_dwpw.hip: a depthwise 3x3 / pad 1 convolution (stride 1 or 2, C channels, H x W -> P x Q) and the 1x1
+// convolution to K channels behind it as one launch.  yd: where the depthwise output goes, or null if nobody
+// reads it later.  y overlaps none of the inputs.
+struct DwPwArgs {
+    const void *x, *wd, *w;
+    const float *bd, *b;
+    void *yd, *y;
+    int N, C, H, W, P, Q, K, stride, relu_d, relu;
+};
+bool dwpw_applicable(const DwPwArgs &a, int n_cu);
+hipError_t launch_dwpw(const DwPwArgs &a, int n_cu, hipStream_t stream);
+
 hipError_t launch_probe(uint32_t *out, int n_blocks, hipStream_t stream);
 // blocks x waves wavefronts of nothing but 32x32x16 bf16 matrix instructions, 64 * iters each; out: one float
 // per thread.  dense: pseudo-random operands in (-1, 1) instead of zeros.

@@ -43,6 +43,9 @@ struct Step {
     bool record;            // a later layer on another lane waits for this one
     bool pool_next;         // CONV: the next layer is a 2x2 / stride 2 max pool that is the only reader of
                             // this layer's output; the pair may run as one launch (conv_pool2_fusable)
+    bool pw_next;           // DWCONV 3x3: the next layer is a plain 1x1 convolution of this layer's output; the pair may
+                            // run as one launch (dwpw_applicable)
+    bool mid_unread;        // with pw_next: this layer's output is overwritten before anybody else could read it
     int chain_len;          // layers from this one on that may run as one launch with a workgroup per image (else 0)
 };
 
@@ -226,6 +229,7 @@ gpulet_status build_plan(const gpulet_model_desc *m, int batch, Plan &plan) {
         s.record = false;
         s.pool_next = false;
         s.chain_len = 0;
+        s.pw_next = s.mid_unread = false;
         int oc = 0, oh = 0, ow = 0, oelem = 2;
         if (L.op == GPULET_OP_CONV) {
             // in_ch_total > 0: the layer reads L.C channels from in_ch_offset on of wider pixels
@@ -378,6 +382,26 @@ gpulet_status build_plan(const gpulet_model_desc *m, int batch, Plan &plan) {
         }
         c.pool_next = only_reader;
     }
+    // Depthwise 3x3 + pointwise pairs.  The pair's output must not lie over its input, which other workgroups
+    // may still read.
+    for (int i = 0; i + 1 < m->n_layers; ++i) {
+        Step &d = plan.steps[static_cast<size_t>(i)];
+        const Step &c = plan.steps[static_cast<size_t>(i + 1)];
+        if (d.op != GPULET_OP_DWCONV || d.k != 3 || d.k2 != 3 || d.pad != 1 || d.stride != 1 || d.out_buf == m->out_buf) continue;
+        if (c.op != GPULET_OP_CONV || c.group_len != 1 || c.in_buf != d.out_buf || c.slice || c.res_buf >= 0 || c.out2_buf >= 0 ||
+            c.pool_buf >= 0 || c.conv.pre_pool || c.conv.x_ch_stride != 0 || c.conv.R != 1 || c.conv.S != 1 ||
+            c.conv.stride != 1 || c.conv.pad != 0 || c.out_buf == d.in_buf)
+            continue;
+        d.pw_next = true;
+        for (int j = i + 2; j < m->n_layers; ++j) {
+            const Step &t = plan.steps[static_cast<size_t>(j)];
+            if (t.in_buf == d.out_buf || t.res_buf == d.out_buf) break;
+            if ((t.out_buf == d.out_buf && !t.slice) || t.pool_buf == d.out_buf) {
+                d.mid_unread = true;
+                break;
+            }
+        }
+    }
     find_chains(plan);
     assign_lanes(plan, m->n_bufs, g_model_lanes.load());
 
@@ -525,6 +549,27 @@ hipError_t enqueue(const Bound &bd, gpulet_partition *p) {
             }
             i += len - 1;
             continue;
+        }
+        if (s.pw_next && !s.record && steps[i + 1].lane == s.lane && steps[i + 1].wait.empty() && !steps[i + 1].record &&
+            conv_fusion_allowed()) {
+            const Step &c = steps[i + 1];
+            DwPwArgs a;
+            a.x = bd.ptr(s.in_buf);
+            a.wd = s.w;
+            a.bd = s.b;
+            a.w = c.conv.w;
+            a.b = c.conv.b;
+            a.yd = s.mid_unread ? nullptr : bd.ptr(s.out_buf);
+            a.y = bd.ptr(c.out_buf);
+            a.N = s.N; a.C = s.C; a.H = s.H; a.W = s.W; a.P = s.P; a.Q = s.Q; a.K = c.conv.K;
+            a.stride = s.stride; a.relu_d = s.relu; a.relu = c.conv.relu;
+            if (dwpw_applicable(a, ctx.n_cu)) {
+                e = launch_dwpw(a, ctx.n_cu, stream);
+                if (e != hipSuccess) return e;
+                p->kernels_enqueued.fetch_add(1);
+                ++i;
+                continue;
+            }
         }
         if (s.op == GPULET_OP_CONV && s.pool_next && !s.record && steps[i + 1].lane == s.lane && steps[i + 1].wait.empty()) {
             // the layer and the max pool behind it as one launch, when a kernel with a pooled

@@ -185,6 +185,10 @@ class DeviceModel:
             if (nd.op == "maxpool" and (nd.attr["k"], nd.attr["stride"], nd.attr["pad"]) == (2, 2, 0) and i > 0
                     and nodes[i - 1].op == "conv" and nodes[i - 1].dst == nd.src):
                 last_use[storage(nodes[i - 1].src)] = max(last_use.get(storage(nodes[i - 1].src), 0), i)
+            # The same for a 1x1 convolution right behind a depthwise 3x3 one.
+            if (nd.op == "conv" and nd.attr["k"] == 1 and i > 0 and nodes[i - 1].op == "dwconv" and nodes[i - 1].dst == nd.src
+                    and nodes[i - 1].attr["k"] == 3):
+                last_use[storage(nodes[i - 1].src)] = max(last_use.get(storage(nodes[i - 1].src), 0), i)
         last_use[storage(model.out)] = len(nodes)
 
         buf_of = {"x": 0, storage(model.out): 1}
