@@ -249,15 +249,16 @@ Choice choose_kernel(const ConvParams &p, bool vec, const LaunchCtx &ctx) {
     int tw64 = 0;
     const bool c64_ok = c64_applicable(p, vec, &tw64);
     if (best == 10 && !c64_ok) best = 1;
-    // Loading 144 registers of weights per consumer pays from about eight pixel tiles per
-    // workgroup on (measured: 3x3 64->64 on 224x224 at batch 32 209 -> 150-160 us, 64->192 on
-    // 56x56 36.6 -> 31.7 us; with three tiles per workgroup, 64->64 on 56x56, it is 9 % slower).
+    // Loading 144 registers of weights per consumer (about 2.5 us) pays from three pixel tiles per workgroup on
+    // where one filter tile covers the layer: 3x3 64 -> 64 on 56x56 at batch 32 16.3 -> 15.6 us, at batch 16 on 128 CUs
+    // 14.1 -> 13.3 (two tiles: 8.1 and 8.9); with several filter tiles, which share a gathered pixel tile, later: 64 ->
+    // 192 on 56x56 at batch 8 on 128 CUs (4.7 tiles) 17.3 -> 16.1, 64 -> 128 on 112x112 at batch 4 (3 tiles) 13.2 and 15.2.
     if (forced < 0 && c64_ok) {
         const int n_cb = (p.Q + tw64 - 1) / tw64;
         const long long tiles_m = ((1LL * p.N * p.P * tw64 + PATCH_BM - 1) / PATCH_BM) * n_cb;
         const int tiles_n = (p.K + 63) / 64;
         const int wgs_per_col = std::max(1, n_cu / tiles_n);
-        if (tiles_m >= 8LL * wgs_per_col) best = 10;
+        if (2 * tiles_m >= (tiles_n == 1 ? 6LL : 9LL) * wgs_per_col) best = 10;
     }
     if (best == 9 && !stem_applicable(p)) best = 1;
     if (forced < 0 && stem_applicable(p)) best = 9;  // by shape alone: the same bits in every batch and gpu-let

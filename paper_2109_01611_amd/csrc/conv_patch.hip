@@ -302,7 +302,7 @@ __global__ __launch_bounds__((4 + NPROD) * 64) void conv3x3_patch_kernel(const C
 // reads for two matrix instructions.  Four producer wavefronts keep the patches
 // of the next tiles in flight (two LDS buffers of 32 KB, DMA loads; a third buffer changed nothing).
 //
-// Per tile every wavefront executes two barriers:
+// Behind barrier B0 the filters are in LDS.  Per tile every wavefront executes two barriers:
 //   B1(t): the patch of tile t has landed (each producer waited for its own
 //          transfers; those of later tiles may still be in flight);
 //   B2(t): the consumers have read the patch of tile t for the last time; the
@@ -317,7 +317,7 @@ __global__ __launch_bounds__((4 + NPROD) * 64) void conv3x3_patch_kernel(const C
 // operand; K % 8 == 0 and a destination that allows aligned 16-byte stores.
 // ---------------------------------------------------------------------------
 // STAMP: the instance that records wall-clock stamps of its first workgroups (gpulet_conv2d_timeline):
-// 0 first instruction, 1 weights requested, and for the workgroup's fourth pixel tile 2 before B1,
+// 0 first instruction, 1 weights in registers or on their way there from LDS, and for the workgroup's fourth pixel tile 2 before B1,
 // 3 patch there (after B1), 4 matrix instructions issued, 5 patch released (after B2), 6 output
 // stores issued, 7 the fifth tile before B1 (tile period = 7 - 2).
 template <bool STAMP>
@@ -335,6 +335,8 @@ __global__ __launch_bounds__(512) void conv3x3_c64_kernel(const ConvParams p, co
     __shared__ __attribute__((aligned(1024))) __bf16 patch[NB * PATCH];
     __shared__ __attribute__((aligned(16))) unsigned char trs[4 * 64 * TROW];
     __shared__ __attribute__((aligned(16))) float lbias[BN];
+    constexpr int WCH = 9 * BK / CHUNK;        // 16-byte chunks per filter
+    __shared__ __attribute__((aligned(1024))) __bf16 wlds[BN * WCH * CHUNK];   // the filters on their way to registers
 
     // Which pixel tiles this workgroup walks: first, stride, count (uniform over the workgroup).
     // Workgroups are dealt round-robin to the eight dies.  When the grid allows it every die
@@ -423,6 +425,7 @@ __global__ __launch_bounds__(512) void conv3x3_c64_kernel(const ConvParams p, co
         };
 #pragma unroll
         for (int t = 0; t < NB; ++t) issue_patch(t);
+        __syncthreads();   // B0
         for (int t = 0; t < T; ++t) {
             __builtin_amdgcn_s_waitcnt(vmcnt_imm((NB - 1) * POPS));  // all but the transfers of later tiles have landed
             __syncthreads();                                         // B1
@@ -435,18 +438,29 @@ __global__ __launch_bounds__(512) void conv3x3_c64_kernel(const ConvParams p, co
         const int frow = lane & 31, fhalf = lane >> 5;
         const int wy = wave >> 1, wx = wave & 1;   // pixel half, filter half
         // The fragments of this wavefront's 32 filters: tap-major, four depth steps of 16 each.
+        // They pass through LDS, in whole lines: loaded as fragments, every instruction touches 32 lines and
+        // the 36 of them take 3.3 us.  A filter is nine rows of 128 bytes, swizzled by the filter like a slice of
+        // the gathering kernel.
         bf16x8 wf[36];
         {
-            const __amdgpu_buffer_rsrc_t rw =
-                __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16 *>(p.w), 0, p.w_bytes, RSRC_FLAGS);
-            const int k = n0 + wx * 32 + frow;
+            const i32x4 rw = make_rsrc(p.w, p.w_bytes);
+            constexpr int PER_WAVE = BN * WCH / 64 / 4;
+            static_assert(BN * WCH % 256 == 0, "whole transfers");
 #pragma unroll
-            for (int i = 0; i < 36; ++i) {
-                const int tap = i >> 2, ks = i & 3;
-                const unsigned off = k < p.K ? static_cast<unsigned>(((k * 9 + tap) * BK + (ks * 2 + fhalf) * CHUNK) * 2) : OOB;
-                const u32x4 raw = __builtin_amdgcn_raw_buffer_load_b128(rw, off, 0, 0);
-                wf[i] = __builtin_bit_cast(bf16x8, raw);
+            for (int i = 0; i < PER_WAVE; ++i) {
+                const int at = (i * 4 + wave) * 64 + lane;
+                const int f = at / WCH, c = at - f * WCH;
+                const int chunk = (c & ~7) | ((c & 7) ^ ((f >> 1) & 7));
+                dma16(rw, lds_addr(wlds) + (i * 4 + wave) * 1024,
+                      n0 + f < p.K ? static_cast<unsigned>(((n0 + f) * WCH + chunk) * 16) : OOB);
             }
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            __syncthreads();   // B0
+            const int f = wx * 32 + frow;
+            const __bf16 *wrow = wlds + f * (WCH * CHUNK);
+#pragma unroll
+            for (int i = 0; i < 36; ++i)
+                wf[i] = *reinterpret_cast<const bf16x8 *>(wrow + (i >> 2) * BK + ((((i & 3) * 2 + fhalf) ^ ((f >> 1) & 7)) * CHUNK));
         }
         st.at(1);
         unsigned char *tr = trs + wave * (64 * TROW);
