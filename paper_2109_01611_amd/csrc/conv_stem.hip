@@ -78,44 +78,6 @@ __global__ __launch_bounds__(256) void conv_stem_kernel(const ConvParams p, cons
     const __amdgpu_buffer_rsrc_t rw =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16 *>(p.w), 0, p.w_bytes, RSRC_FLAGS);
 
-    // Weights -> LDS as [filter][r][s][4], zero where s >= S, c >= C or the filter does not exist.
-    // Eight loads are issued before the first is used: one load-use chain per element would
-    // cost a memory latency each, which is most of the life of a workgroup at small batches.
-    {
-        unsigned short *wl = reinterpret_cast<unsigned short *>(stg_raw);
-        constexpr int WPT = (WELEMS + 255) / 256, WB = 8;
-#pragma unroll
-        for (int i0 = 0; i0 < WPT; i0 += WB) {
-            unsigned short v[WB];
-#pragma unroll
-            for (int u = 0; u < WB; ++u) {
-                const int i = tid + (i0 + u) * 256;
-                const int f = i / (R * KROW), rem = i - f * (R * KROW);
-                const int r = rem / KROW, kk = rem - r * KROW;
-                const int sx = kk >> 2, c = kk & 3;
-                const bool ok = i < WELEMS && n0 + f < p.K && sx < p.S && c < p.C;
-                const unsigned off = ok ? static_cast<unsigned>(((((n0 + f) * R + r) * p.S + sx) * p.C + c) * 2) : OOB;
-                v[u] = __builtin_amdgcn_raw_buffer_load_b16(rw, off, 0, 0);
-            }
-#pragma unroll
-            for (int u = 0; u < WB; ++u) {
-                const int i = tid + (i0 + u) * 256;
-                if (i < WELEMS) wl[i] = v[u];
-            }
-        }
-    }
-    __syncthreads();
-    bf16x8 wf[R][KS][NT];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int j = 0; j < KS; ++j)
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-                wf[r][j][t] = *reinterpret_cast<const bf16x8 *>(stg_raw + 2 * ((t * 32 + frow) * (R * KROW) + r * KROW +
-                                                                                 j * 16 + fhalf * 8));
-    if (tid < BN) lbias[tid] = (p.b && n0 + tid < p.K) ? p.b[n0 + tid] : 0.f;
-
     // Tile t of this workgroup: image n, first output row p0 and column q0.
     struct Tile {
         int n, p0, q0;
@@ -171,6 +133,73 @@ __global__ __launch_bounds__(256) void conv_stem_kernel(const ConvParams p, cons
         }
     };
 
+    // The patch of tile t+1 is written to LDS during tile t and was requested during tile t-1:
+    // a tile is too short to hide a memory latency itself.
+    uint2 nxt[STEM_PXT], nxt2[STEM_PXT];
+    Tile cur = tile_at(0), nx = cur;
+    fetch(cur, nxt);
+    const float bias0 = tid < BN && p.b && n0 + tid < p.K ? p.b[n0 + tid] : 0.f;
+
+    // Weights -> LDS as [filter][r][s][4], zero where s >= S, c >= C or the filter does not exist.  All loads are
+    // issued before the first is used, behind those of the first patch: a workgroup starts with one memory
+    // latency.  (Eight 2-byte loads at a time were seven latencies: 7x7 on 224x224 at batch 1 9.0 us, now 5.7, at batch 32
+    // 25.5 and 22.4, on 128 CUs 37.7 and 34.1.)
+    unsigned short *wl = reinterpret_cast<unsigned short *>(stg_raw);
+    if (p.C == 4 && (reinterpret_cast<uintptr_t>(p.w) & 7) == 0) {
+        constexpr int WPX = WELEMS / 4, WPT = (WPX + 255) / 256;   // filter pixels of four channels
+        uint2 v[WPT];
+#pragma unroll
+        for (int u = 0; u < WPT; ++u) {
+            const int i = tid + u * 256;
+            const int f = i / (R * KROW / 4), rem = i - f * (R * KROW / 4);
+            const int r = rem / (KROW / 4), sx = rem - r * (KROW / 4);
+            const bool ok = i < WPX && n0 + f < p.K && sx < p.S;
+            const auto w = __builtin_amdgcn_raw_buffer_load_b64(rw, ok ? static_cast<unsigned>((((n0 + f) * R + r) * p.S + sx) * 8) : OOB, 0, 0);
+            v[u] = make_uint2(w[0], w[1]);
+        }
+#pragma unroll
+        for (int u = 0; u < WPT; ++u)
+            if (tid + u * 256 < WPX) *reinterpret_cast<uint2 *>(wl + (tid + u * 256) * 4) = v[u];
+    } else {
+        constexpr int WPT = (WELEMS + 255) / 256, WB = WPT < 32 ? WPT : 32;
+#pragma unroll
+        for (int i0 = 0; i0 < WPT; i0 += WB) {
+            unsigned short v[WB];
+#pragma unroll
+            for (int u = 0; u < WB; ++u) {
+                const int i = tid + (i0 + u) * 256;
+                const int f = i / (R * KROW), rem = i - f * (R * KROW);
+                const int r = rem / KROW, kk = rem - r * KROW;
+                const int sx = kk >> 2, c = kk & 3;
+                const bool ok = i < WELEMS && n0 + f < p.K && sx < p.S && c < p.C;
+                const unsigned off = ok ? static_cast<unsigned>(((((n0 + f) * R + r) * p.S + sx) * p.C + c) * 2) : OOB;
+                v[u] = __builtin_amdgcn_raw_buffer_load_b16(rw, off, 0, 0);
+            }
+#pragma unroll
+            for (int u = 0; u < WB; ++u) {
+                const int i = tid + (i0 + u) * 256;
+                if (i < WELEMS) wl[i] = v[u];
+            }
+        }
+    }
+    if (tid < BN) lbias[tid] = bias0;
+    stash(0, nxt);
+    __syncthreads();   // (the first barrier of the tile loop then frees the weights' staging area)
+    bf16x8 wf[R][KS][NT];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int j = 0; j < KS; ++j)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                wf[r][j][t] = *reinterpret_cast<const bf16x8 *>(stg_raw + 2 * ((t * 32 + frow) * (R * KROW) + r * KROW +
+                                                                                 j * 16 + fhalf * 8));
+
+    if (T > 1) {
+        nx = tile_at(1);
+        fetch(nx, nxt);
+    }
+
     // Registers -> memory for one wavefront's 32 pixels x BN filters.  Accumulator register v of
     // a lane belongs to filter 8*(v/4) + 4*(lane/32) + v%4 of its 32 and to pixel lane%32, so a
     // lane holds 8-byte pieces of one pixel.  They pass through a region of LDS private to the
@@ -209,16 +238,6 @@ __global__ __launch_bounds__(256) void conv_stem_kernel(const ConvParams p, cons
         __builtin_amdgcn_wave_barrier();
     };
 
-    // The patch of tile t+1 is written to LDS during tile t and was requested during tile t-1:
-    // a tile is too short to hide a memory latency itself.
-    uint2 nxt[STEM_PXT], nxt2[STEM_PXT];
-    Tile cur = tile_at(0), nx = cur;
-    fetch(cur, nxt);
-    stash(0, nxt);  // (the first barrier of the tile loop also frees the weights' staging area)
-    if (T > 1) {
-        nx = tile_at(1);
-        fetch(nx, nxt);
-    }
     // One tile: `have` holds the patch of tile t+1, `want` receives that of tile t+2 (the two
     // register sets swap roles every tile, so no copy has to wait for a load).
     auto one_tile = [&](int t, const uint2 (&have)[STEM_PXT], uint2 (&want)[STEM_PXT]) {
