@@ -625,6 +625,11 @@ __global__ __launch_bounds__((CWM * CWN + NPROD) * 64, waves_per_simd(BM, BN, NS
 template <int BM, int BN, int CWM, int CWN, int NPROD, int NS, Depth DEPTH, int MF, int SPB>
 __global__ __launch_bounds__((CWM * CWN + NPROD) * 64, waves_per_simd(BM, BN, NS, SPB, CWM * CWN + NPROD)) void conv_igemm_group_kernel(const ConvGroup g) {
     const int b = blockIdx.x;
+    // The lines of every member's block are requested with the table of first workgroups: which member it is decides
+    // only what is read from the scalar cache then.
+#pragma unroll
+    for (int i = 0; i < MAX_GROUP; ++i)
+        asm volatile("" ::"s"(g.p[i].x), "s"(g.p[i].S), "s"(g.p[i].x_bytes), "s"(g.p[i].d_s.mul), "s"(g.first[i]));
     int j = 0;
 #pragma unroll
     for (int i = 1; i < MAX_GROUP; ++i)

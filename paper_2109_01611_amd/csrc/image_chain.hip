@@ -63,21 +63,24 @@ struct ChainParams {
     FastDiv d_in_wide;
     // What is copied to LDS at once, while the first layer runs, and behind the second layer (over the first two
     // tensors).  The last two hold weights of fully connected layers.
+    int n_bias, n_first, n_second, n_third;
     Staged bias[kMaxChain], first[kMaxChain], second[kMaxChain], third[kMaxChain];
     ChainOp op[kMaxChain];
 };
 
-// A layer's description in one round trip to the scalar cache: read where they are needed, its fields would be
-// half a dozen dependent loads of a few hundred cycles each in front of every layer.
-__device__ __forceinline__ ChainOp fetch_op(const ChainOp &g) {
-    const ChainOp o = g;
-    asm volatile("" ::"s"(o.y), "s"(o.kind), "s"(o.C), "s"(o.H), "s"(o.W), "s"(o.K), "s"(o.P), "s"(o.Q),
-                 "s"(o.S), "s"(o.stride), "s"(o.pad), "s"(o.relu), "s"(o.out_fp32), "s"(o.src), "s"(o.src_w), "s"(o.dst_0),
-                 "s"(o.dst_w), "s"(o.weights), "s"(o.table), "s"(o.bias), "s"(o.zeros), "s"(o.Kg), "s"(o.chunks), "s"(o.taps));
-    asm volatile("" ::"s"(o.d_q.mul), "s"(o.d_q.shift), "s"(o.d_cv.mul), "s"(o.d_cv.shift), "s"(o.d_kv.mul),
-                 "s"(o.d_kv.shift), "s"(o.d_s.mul), "s"(o.d_s.shift), "s"(o.d_rs.mul), "s"(o.d_rs.shift));
-    return o;
-}
+// What a layer needs of its description, in one round trip to the scalar cache: read where they are needed, the fields
+// would be half a dozen dependent loads of a few hundred cycles each in front of every layer.  No more than that: the
+// whole description, or two of them, does not fit the scalar registers, and the spills cost the convolutions 1-2 us.
+#define FETCH_CONV(o) \
+    asm volatile("" ::"s"((o).C), "s"((o).K), "s"((o).P), "s"((o).Q), "s"((o).stride), "s"((o).relu), "s"((o).src), "s"((o).src_w), \
+                 "s"((o).dst_0), "s"((o).dst_w), "s"((o).weights), "s"((o).table), "s"((o).bias), "s"((o).Kg), "s"((o).chunks), \
+                 "s"((o).d_q.mul), "s"((o).d_q.shift))
+#define FETCH_POOL(o) \
+    asm volatile("" ::"s"((o).C), "s"((o).H), "s"((o).W), "s"((o).P), "s"((o).Q), "s"((o).stride), "s"((o).pad), "s"((o).src), \
+                 "s"((o).src_w), "s"((o).dst_0), "s"((o).dst_w), "s"((o).d_q.mul), "s"((o).d_q.shift), "s"((o).d_cv.mul), "s"((o).d_cv.shift))
+#define FETCH_FC(o) \
+    asm volatile("" ::"s"((o).K), "s"((o).Kg), "s"((o).src), "s"((o).weights), "s"((o).zeros), "s"((o).bias), "s"((o).dst_0), \
+                 "s"((o).relu), "s"((o).out_fp32))
 
 // Barrier between layers: LDS is all they share, so nobody waits for memory.
 __device__ __forceinline__ void lds_barrier() {
@@ -91,7 +94,9 @@ __device__ __forceinline__ void lds_barrier() {
 // and one 8-byte store per item.  The weights of 16 filters stay in the wavefront's registers for all of
 // its pixel tiles.  Instruction issue bounds this loop (four wavefronts per SIMD, depths of a few hundred).
 template <int STEPS>   // depth steps of 32
-__device__ __forceinline__ void chain_conv(const ChainOp &o, char *lds, int wave, int lane) {
+__device__ __forceinline__ void chain_conv(const ChainOp &g, char *lds, int wave, int lane) {
+    const ChainOp o = g;
+    FETCH_CONV(o);
     const int sub = lane & 15, kq = lane >> 4;
     const int M = o.P * o.Q, m_tiles = (M + 15) / 16;
     const int px_step = o.stride * o.C * 2, row_step = o.src_w * px_step;
@@ -136,7 +141,9 @@ __device__ __forceinline__ void chain_conv(const ChainOp &o, char *lds, int wave
 // Max pool: 8 channels of one output pixel per thread, window coordinates clamped to the image,
 // maximum on order-preserving integer keys (as pool_max_item).
 template <int S>
-__device__ __forceinline__ void chain_pool(const ChainOp &o, char *lds) {
+__device__ __forceinline__ void chain_pool(const ChainOp &g, char *lds) {
+    const ChainOp o = g;
+    FETCH_POOL(o);
     const int cv = o.C / 8, items = o.P * o.Q * cv;
     for (int it = threadIdx.x; it < items; it += kThreads) {
         const int m = fdiv(it, o.d_cv), c8 = it - m * cv;
@@ -256,11 +263,10 @@ __global__ __launch_bounds__(kThreads) void image_chain_kernel(const ChainParams
         return inside ? x[r * c.in_row + q] : make_uint4(0u, 0u, 0u, 0u);
     };
     const uint4 x0 = in_chunk(tid);
-#pragma unroll
-    for (int i = 0; i < kMaxChain; ++i) {
-        if (c.bias[i].bytes > 0) stage_bias(c.bias[i], lds, wave, lane);
-        if (c.first[i].bytes > 0) stage(c.first[i], lds, wave, lane);
-    }
+#pragma unroll 1
+    for (int i = 0; i < c.n_bias; ++i) stage_bias(c.bias[i], lds, wave, lane);
+#pragma unroll 1
+    for (int i = 0; i < c.n_first; ++i) stage(c.first[i], lds, wave, lane);
 
     // All other tensors start as zeros: their borders and tails stay so.
     for (int at = c.in_chunks * 16 + tid * 16; at < c.lds_tensors; at += kThreads * 16)
@@ -312,12 +318,11 @@ __global__ __launch_bounds__(kThreads) void image_chain_kernel(const ChainParams
             y[j] = *reinterpret_cast<const uint4 *>(lds + o.dst_0 + ((p * o.dst_w + q) * o.K + c8 * 8) * 2);
         }
     };
-#pragma unroll
-    for (int i = 0; i < kMaxChain; ++i)
-        if (c.second[i].bytes > 0) stage(c.second[i], lds, wave, lane);
+#pragma unroll 1
+    for (int i = 0; i < c.n_second; ++i) stage(c.second[i], lds, wave, lane);
     bool pending = true;   // weights of fully connected layers are on their way
-    ChainOp o = fetch_op(c.op[0]);
     for (int i = 0;; ++i) {
+        const ChainOp &o = c.op[i];
         if (o.kind == GPULET_OP_CONV) {
             switch ((o.chunks + 3) / 4) {
                 case 1: chain_conv<1>(o, lds, wave, lane); break;
@@ -335,6 +340,7 @@ __global__ __launch_bounds__(kThreads) void image_chain_kernel(const ChainParams
             else
                 chain_pool<2>(o, lds);
         } else {
+            FETCH_FC(o);
             if (pending) {
                 __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
                 lds_barrier();
@@ -361,19 +367,14 @@ __global__ __launch_bounds__(kThreads) void image_chain_kernel(const ChainParams
                     *reinterpret_cast<__bf16 *>(lds + o.dst_0 + tid * 2) = static_cast<__bf16>(v);
             }
         }
-        const ChainOp next = fetch_op(c.op[min(i + 1, c.n_ops - 1)]);
         lds_barrier();
         if (i == 1) {
-#pragma unroll
-            for (int e = 0; e < kMaxChain; ++e)
-                if (c.third[e].bytes > 0) {
-                    stage(c.third[e], lds, wave, lane);
-                    pending = true;
-                }
+#pragma unroll 1
+            for (int e = 0; e < c.n_third; ++e) stage(c.third[e], lds, wave, lane);
+            pending = pending || c.n_third > 0;
         }
         to_memory(o);
         if (i + 1 == c.n_ops) break;
-        o = next;
     }
 }
 
@@ -455,7 +456,7 @@ bool chain_params(const ChainLayer *l, int n, ChainParams &c) {
     }
     c.lds_tensors = at;
     at = align_up(at, 256);
-    for (int i = 0; i < kMaxChain; ++i) c.bias[i] = c.first[i] = c.second[i] = c.third[i] = Staged{};
+    c.n_bias = c.n_first = c.n_second = c.n_third = 0;
     for (int i = 0; i < n; ++i) {
         ChainOp &o = c.op[i];
         if (o.kind == GPULET_OP_CONV) {
@@ -464,7 +465,7 @@ bool chain_params(const ChainLayer *l, int n, ChainParams &c) {
         }
         if (o.kind != GPULET_OP_POOL && l[i].b) {
             o.bias = at;
-            c.bias[i] = Staged{l[i].b, o.K * 4, at};
+            c.bias[c.n_bias++] = Staged{l[i].b, o.K * 4, at};
             at += align_up(o.K * 4, kBiasPiece);
         }
     }
@@ -479,12 +480,15 @@ bool chain_params(const ChainLayer *l, int n, ChainParams &c) {
         const int bytes = o.K * o.Kg * 2, room = align_up(bytes, kPiece);
         if (o.kind == GPULET_OP_FC && n_fc++ > 0 && i >= 3 && over + room <= two_tensors) {
             o.weights = over;
-            c.third[i] = Staged{l[i].w, bytes, over};
+            c.third[c.n_third++] = Staged{l[i].w, bytes, over};
             over += room;
             continue;
         }
         o.weights = at;
-        (o.kind == GPULET_OP_FC ? c.second : c.first)[i] = Staged{l[i].w, bytes, at};
+        if (o.kind == GPULET_OP_FC)
+            c.second[c.n_second++] = Staged{l[i].w, bytes, at};
+        else
+            c.first[c.n_first++] = Staged{l[i].w, bytes, at};
         at += room;
         if (at > kLdsBytes) return false;
     }
