@@ -83,6 +83,8 @@ __global__ __launch_bounds__(NW * 64) void fc_kernel(const FcParams p) {
     const int s_begin = wave * per_wave;
     const int s_end = min(steps, s_begin + per_wave);
 
+    // requested here: behind the sums its latency would stand in front of the stores
+    const float bias = (p.b && o_ok) ? p.b[o] : 0.f;
     f32x4 acc[NB];
 #pragma unroll
     for (int t = 0; t < NB; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -136,7 +138,6 @@ __global__ __launch_bounds__(NW * 64) void fc_kernel(const FcParams p) {
     if (wave != 0) return;
 
     // Accumulator register v of a lane holds batch row 4*(lane/16) + v, output lane%16.
-    const float bias = (p.b && o_ok) ? p.b[o] : 0.f;
 #pragma unroll
     for (int t = 0; t < NB; ++t) {
 #pragma unroll
@@ -202,6 +203,9 @@ __global__ __launch_bounds__(1024) void fc_split_kernel(const FcParams p, float 
     const int s_begin = r_begin + wave * per_wave;
     const int s_end = min(r_end, s_begin + per_wave);
 
+    float bias[OB];   // requested early, as above
+#pragma unroll
+    for (int j = 0; j < OB; ++j) bias[j] = p.b && o_ok[j] ? p.b[o0 + j * 16 + sub] : 0.f;
     f32x4 acc[NB][OB];
 #pragma unroll
     for (int t = 0; t < NB; ++t)
@@ -301,14 +305,13 @@ __global__ __launch_bounds__(1024) void fc_split_kernel(const FcParams p, float 
     for (int j = 0; j < OB; ++j) {
         const int o = o0 + j * 16 + sub;
         if (!o_ok[j]) continue;
-        const float bias = p.b ? p.b[o] : 0.f;
 #pragma unroll
         for (int t = 0; t < NB; ++t)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int n = t * 16 + 4 * kq + v;
                 if (n >= p.N) continue;
-                float val = acc[t][j][v] + bias;
+                float val = acc[t][j][v] + bias[j];
                 if (p.relu) val = val > 0.f ? val : 0.f;
                 const size_t idx = static_cast<size_t>(n) * p.Out + o;
                 if (p.out_fp32)
