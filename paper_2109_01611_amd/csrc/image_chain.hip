@@ -490,8 +490,8 @@ bool chain_params(const ChainLayer *l, int n, ChainParams &c) {
         else
             c.first[c.n_first++] = Staged{l[i].w, bytes, at};
         at += room;
-        if (at > kLdsBytes) return false;
     }
+    if (at > kLdsBytes) return false;   // nothing above lies higher, tables and zeros of a run without weights included
     c.n_ops = n;
     c.d_in_wide = make_fastdiv(c.in_wide);
     return true;
