@@ -565,6 +565,9 @@ gpulet_status gpulet_model_buffer_info(const gpulet_model_desc *m, int batch, in
  * input batch (batch*in_H*in_W*in_C bf16), `out` receives the output buffer.
  * `workspace` must be 256-byte aligned device memory of at least
  * gpulet_model_workspace_bytes() bytes (GPULET_ENOMEM otherwise).
+ * Where `in`, `out` and `workspace` overlap, every layer is a launch of its own
+ * (a launch that stands for several layers would store to the output while it
+ * still reads the input), and no layer may read what it writes itself.
  * If latency_ms is not NULL the call brackets the batch with events, waits
  * for it and stores the elapsed milliseconds; if NULL it returns right after
  * enqueueing.  Counts one batch and `batch` images on the partition.

@@ -429,6 +429,19 @@ struct Bound {
     }
 };
 
+// Whether input, output and workspace share no byte.  A launch that stands for several layers needs that: buffer
+// numbers say what a layer must wait for, and two buffers at one address would let one workgroup store over what
+// another has yet to read.  Without it layers go out one by one.
+bool apart(const Bound &bd) {
+    auto bytes = [&](int buf) { return bd.plan->bufs[static_cast<size_t>(buf)].bytes_per_image * static_cast<size_t>(bd.batch); };
+    const uintptr_t at[3] = {reinterpret_cast<uintptr_t>(bd.in), reinterpret_cast<uintptr_t>(bd.out), reinterpret_cast<uintptr_t>(bd.ws)};
+    const size_t n[3] = {bytes(bd.plan->in_buf), bytes(bd.plan->out_buf), bd.plan->ws_bytes};
+    for (int i = 0; i < 3; ++i)
+        for (int j = 0; j < i; ++j)
+            if (n[i] > 0 && n[j] > 0 && at[i] < at[j] + n[j] && at[j] < at[i] + n[i]) return false;
+    return true;
+}
+
 // Event number `idx` of the gpu-let's pool (created on first use, never timed).
 hipError_t pool_event(gpulet_partition *p, size_t idx, hipEvent_t *ev) {
     while (p->events.size() <= idx) {
@@ -464,6 +477,7 @@ bool chain_aligned(const ChainLayer *l, size_t n, const void *x) {
 // complete, for anything enqueued there afterwards, when this returns.
 hipError_t enqueue(const Bound &bd, gpulet_partition *p) {
     const std::vector<Step> &steps = bd.plan->steps;
+    const bool share = apart(bd);
     bool lane_used[kMaxLanes] = {false};
     for (const Step &s : steps) lane_used[s.lane] = true;
     // events 0 .. kMaxLanes-1: fork and joins; kMaxLanes + i: layer i
@@ -494,7 +508,7 @@ hipError_t enqueue(const Bound &bd, gpulet_partition *p) {
             if (e == hipSuccess) e = hipStreamWaitEvent(stream, ev, 0);
             if (e != hipSuccess) return e;
         }
-        if (s.chain_len > 0 && chain_allowed(steps, i)) {
+        if (share && s.chain_len > 0 && chain_allowed(steps, i)) {
             ChainLayer l[kMaxChain];
             const size_t n = static_cast<size_t>(s.chain_len);
             for (size_t k = 0; k < n; ++k) {
@@ -515,7 +529,7 @@ hipError_t enqueue(const Bound &bd, gpulet_partition *p) {
         }
         // A launch group whose members all sit on this lane goes out as one launch, after the
         // waits of every member; otherwise its members are launched one by one as usual.
-        size_t len = s.group_len > 1 ? static_cast<size_t>(s.group_len) : 1;
+        size_t len = share && s.group_len > 1 ? static_cast<size_t>(s.group_len) : 1;
         for (size_t k = 1; k < len; ++k)
             if (steps[i + k].lane != s.lane) len = 1;
         if (len > 1) {
@@ -550,7 +564,7 @@ hipError_t enqueue(const Bound &bd, gpulet_partition *p) {
             i += len - 1;
             continue;
         }
-        if (s.pw_next && !s.record && steps[i + 1].lane == s.lane && steps[i + 1].wait.empty() && !steps[i + 1].record &&
+        if (share && s.pw_next && !s.record && steps[i + 1].lane == s.lane && steps[i + 1].wait.empty() && !steps[i + 1].record &&
             conv_fusion_allowed()) {
             const Step &c = steps[i + 1];
             DwPwArgs a;
@@ -571,7 +585,7 @@ hipError_t enqueue(const Bound &bd, gpulet_partition *p) {
                 continue;
             }
         }
-        if (s.op == GPULET_OP_CONV && s.pool_next && !s.record && steps[i + 1].lane == s.lane && steps[i + 1].wait.empty()) {
+        if (share && s.op == GPULET_OP_CONV && s.pool_next && !s.record && steps[i + 1].lane == s.lane && steps[i + 1].wait.empty()) {
             // the layer and the max pool behind it as one launch, when a kernel with a pooled
             // epilogue applies and does not cost the layer more than the pool kernel saves
             ConvArgs a = s.conv;

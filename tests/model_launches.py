@@ -28,10 +28,10 @@ def model_launches(tmp_path_factory):
         """``layers``: dicts of ``gpulet_layer`` fields (a missing ``bias`` means one is there) -> [(kernel, layers run), ...]"""
         rows = []
         for l in layers:
-            f = dict(res_buf=-1, K=0, R=0, S=0, stride=0, pad=0, relu=0, mode=0, out_fp32=0, bias=1)
+            f = dict(res_buf=-1, K=0, R=0, S=0, stride=0, pad=0, relu=0, mode=0, out_fp32=0, group_next=0, bias=1)
             f.update(l)
             rows.append(" ".join(str(int(f[n])) for n in ("op", "in_buf", "out_buf", "res_buf", "C", "K", "R", "S", "stride", "pad",
-                                                             "relu", "mode", "out_fp32", "bias")))
+                                                             "relu", "mode", "out_fp32", "group_next", "bias")))
         text = "%d %d %d %x %x %d %d %d %d %d %d %d\n%s\n" % (
             (cu, batch, split_k, in_at, out_at, len(layers), n_bufs or len(layers) + 1) + tuple(in_shape) + (in_buf, out_buf, "\n".join(rows)))
         out = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=120, check=True).stdout.split("\n")

@@ -2,7 +2,8 @@
 // the library's own (this program comes first in symbol resolution).  No device is touched; the pointers are
 // made up and never followed.  Reads requests
 //   n_cu batch split_k in_at out_at n_layers n_bufs C H W in_buf out_buf
-// followed by the layers, "op in_buf out_buf res_buf C K R S stride pad relu mode out_fp32 bias" each.  The input lies at
+// followed by the layers, "op in_buf out_buf res_buf C K R S stride pad relu mode out_fp32 group_next
+// bias" each.  The input lies at
 // in_at, the output at out_at, and the workspace at kWorkspace; bias 0 stands for no bias.  Prints a line per launch: the
 // kernel and how many layers it runs.
 #include <cstdio>
@@ -57,8 +58,8 @@ int main() {
         for (gpulet_layer &y : l) {
             y = gpulet_layer{};
             int bias = 0;
-            if (std::scanf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d", &y.op, &y.in_buf, &y.out_buf, &y.res_buf, &y.C, &y.K, &y.R,
-                           &y.S, &y.stride, &y.pad, &y.relu, &y.mode, &y.out_fp32, &bias) != 14)
+            if (std::scanf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d", &y.op, &y.in_buf, &y.out_buf, &y.res_buf, &y.C, &y.K, &y.R,
+                           &y.S, &y.stride, &y.pad, &y.relu, &y.mode, &y.out_fp32, &y.group_next, &bias) != 15)
                 return 1;
             y.w = reinterpret_cast<void *>(kWeights);
             y.b = bias ? reinterpret_cast<float *>(kWeights) : nullptr;

@@ -63,3 +63,20 @@ def test_layers_of_one_launch_leave_what_separate_launches_leave(model, batch, p
             tensors[fused] = [y.clone()] + [dm.read_tensor(t, batch) for t in named]
     for a, b in zip(*tensors.values()):
         assert torch.equal(a, b)
+
+
+def test_an_output_inside_the_input():
+    # separate launches: the first layer has read the whole batch before the last one stores
+    model, batch = workloads.lenet5(), 40
+    dm = lowering.DeviceModel(model, workloads.parameters(model, 4), DEV)
+    with gpulet.Partition(0, 100, 0) as p:
+        xd = dm.input_to_device(workloads.batch_input(model, batch, 4))
+        want, _ = dm.run(p, xd)
+        ws, n = dm.workspace(batch)
+        over = xd.view(torch.float32).flatten()[:want.numel()]
+        before = p.kernel_launches()
+        torch.cuda.synchronize()
+        gpulet.run_model(dm.desc, batch, p, xd, over, ws, n)
+        p.sync()
+        assert p.kernel_launches() - before == dm.desc.n_layers
+        assert torch.equal(over.view_as(want), want)
