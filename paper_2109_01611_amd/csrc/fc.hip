@@ -344,7 +344,7 @@ struct SplitPlan {
 
 SplitPlan plan_split(int N, int In, int Out, int n_cu) {
     SplitPlan s;
-    s.wide = In >= 8192 && N <= 32;
+    s.wide = In >= kFcLongRow && N <= 32;
     s.groups = (Out + 63) / 64;
     s.ksplit = s.wide ? std::max(1, std::min(8, (n_cu < 1 ? 1 : n_cu) / s.groups)) : 1;
     s.need = s.ksplit > 1 ? static_cast<size_t>(s.groups) * s.ksplit * (N <= 16 ? 1 : 2) * 4 * 64 * 16 : 0;
@@ -394,7 +394,7 @@ hipError_t launch_fc(const void *x, const void *w, const float *b, void *y, int 
     p.N = N; p.In = In; p.Out = Out; p.relu = relu; p.out_fp32 = out_fp32;
     const bool vec = (In % 8 == 0) && (reinterpret_cast<uintptr_t>(x) % 16 == 0) &&
                      (reinterpret_cast<uintptr_t>(w) % 16 == 0);
-    const bool wide = In >= 8192;  // long rows: 16 wavefronts per workgroup
+    const bool wide = In >= kFcLongRow;  // long rows: 16 wavefronts per workgroup
     const SplitPlan plan = plan_split(N, In, Out, ctx.n_cu);
     if (plan.wide) {
         // The depth ranges need scratch for the partial tiles and one counter per output group,

@@ -123,6 +123,7 @@ void set_conv_tile(int tile);
 void set_conv_split_k(int max_split);
 hipError_t launch_pool(const void *x, void *y, int N, int C, int H, int W, int P, int Q, int mode,
                        int k, int stride, int pad, hipStream_t stream);
+constexpr int kFcLongRow = 8192;   // rows from here on are split over 16 wavefronts and more (fc.hip), below over four
 hipError_t launch_fc(const void *x, const void *w, const float *b, void *y, int N, int In, int Out,
                      int relu, int out_fp32, const LaunchCtx &ctx, hipStream_t stream);
 // The layer with its scratch in the library's static device array (no allocation anywhere);

@@ -393,7 +393,8 @@ bool chain_params(const ChainLayer *l, int n, ChainParams &c) {
         o.kind = s.kind; o.C = s.C; o.H = s.H; o.W = s.W; o.K = s.K; o.P = s.P; o.Q = s.Q; o.S = s.S;
         o.stride = s.stride; o.pad = s.pad; o.relu = s.relu; o.out_fp32 = s.out_fp32;
         if (s.kind == GPULET_OP_FC) {
-            if (1LL * s.C * s.H * s.W > kLdsBytes) return false;
+            // longer rows are not added in four quarters by the kernel that runs the layer alone
+            if (1LL * s.C * s.H * s.W >= kFcLongRow) return false;
             o.Kg = s.C * s.H * s.W;
             // whole 16-byte transfers
             if (2LL * o.Kg * s.K > kLdsBytes || o.Kg * s.K % 8 != 0 || s.K > kThreads) return false;
