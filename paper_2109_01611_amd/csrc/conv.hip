@@ -266,6 +266,9 @@ Choice choose_kernel(const ConvParams &p, bool vec, const LaunchCtx &ctx) {
     return Choice{best, best_split, tw, tw64, th11, tw11, patch_tile, (is_gathering_tile(best) || best == 11) ? best_cost : 0.0};
 }
 
+// Only the gathering tiles split.
+bool splits_depth(const Choice &c) { return is_gathering_tile(c.best) && c.split > 1; }
+
 }  // namespace
 
 hipError_t launch_conv(const ConvArgs &a, const LaunchCtx &ctx, hipStream_t stream) {
@@ -325,10 +328,18 @@ bool conv_pool2_fusable(const ConvArgs &a, const LaunchCtx &ctx) {
     int th = 0, tw = 0;
     double geo = 0.0;
     const Choice c = choose_kernel(p, vec, ctx);
+    if (splits_depth(c)) return false;   // partial sums: other bits than the pooled epilogue's
     if (c.best == 10) return c64_applicable(p, vec, &tw, true);   // the same kernel with another epilogue
     if (p.C < 2 * BK || !tall_eligible(p, vec, &th, &tw, &geo, true)) return false;
     if (c.cost <= 0.0) return false;
     return tall_cost(p, th, tw, geo, ctx.n_cu < 1 ? 1 : ctx.n_cu) <= 1.15 * c.cost;
+}
+
+bool conv_splits_depth(const ConvArgs &a, const LaunchCtx &ctx) {
+    if (g_max_split_k.load() <= 1) return false;
+    ConvParams p;
+    bool vec = false;
+    return make_params(a, ctx, p, vec) == hipSuccess && splits_depth(choose_kernel(p, vec, ctx));
 }
 
 // Independent layers in one launch.  Every member must be a layer the gathering kernel would
@@ -347,7 +358,7 @@ hipError_t launch_conv_group(const ConvArgs *a, int n, const LaunchCtx &ctx, hip
             break;
         }
         const Choice c = choose_kernel(p[j], vec, ctx);
-        if (!is_gathering_tile(c.best) || c.split > 1) together = false;
+        if (!is_gathering_tile(c.best) || splits_depth(c)) together = false;
     }
     if (launches) *launches = together ? 1 : n;
     if (!together) {

@@ -114,6 +114,8 @@ bool conv_pool2_fusable(const ConvArgs &a, const LaunchCtx &ctx);
 void set_conv_pool_fusion(int on);
 // Whether layers of different kinds may share a launch: not while pool fusion is switched off or a tile is forced.
 bool conv_fusion_allowed();
+// Whether launch_conv would split the layer's depth over several workgroups (then it adds in another order).
+bool conv_splits_depth(const ConvArgs &a, const LaunchCtx &ctx);
 // n independent layers (no member reads or overwrites what another writes), in one launch where
 // the kernels allow it.
 // *launches (if not null) receives the number of kernel launches made: 1 or n.

@@ -577,7 +577,10 @@ hipError_t enqueue(const Bound &bd, gpulet_partition *p) {
             a.y = bd.ptr(c.out_buf);
             a.N = s.N; a.C = s.C; a.H = s.H; a.W = s.W; a.P = s.P; a.Q = s.Q; a.K = c.conv.K;
             a.stride = s.stride; a.relu_d = s.relu; a.relu = c.conv.relu;
-            if (dwpw_applicable(a, ctx.n_cu)) {
+            ConvArgs pw = c.conv;
+            pw.x = bd.ptr(c.in_buf);
+            pw.y = a.y;
+            if (dwpw_applicable(a, ctx.n_cu) && !conv_splits_depth(pw, ctx)) {
                 e = launch_dwpw(a, ctx.n_cu, stream);
                 if (e != hipSuccess) return e;
                 p->kernels_enqueued.fetch_add(1);

@@ -66,6 +66,14 @@ def test_pairs_that_stay_two_launches(case):
     _both_ways(_pair(C, H, W, K, True, stride), batch, pct, 2)
 
 
+def test_a_depth_split_keeps_its_sums():
+    gpulet.set_conv_split_k(8)
+    try:
+        _both_ways(_pair(512, 10, 10, 512), 1, 100, 2)
+    finally:
+        gpulet.set_conv_split_k(1)
+
+
 @pytest.mark.parametrize("reuse", [True, False])
 def test_whole_model_with_and_without_shared_launches(reuse):
     model = workloads.ssd_mobilenet()

@@ -1,4 +1,4 @@
-"""When layers that may share a launch do not: input, output and workspace that overlap."""
+"""When layers that may share a launch do not: input, output and workspace that overlap, a depth split."""
 
 import pytest
 
@@ -32,3 +32,10 @@ def test_overlapping_buffers_keep_layers_apart(model_launches, case):  # noqa: F
     for out_at in (INPUT, INPUT + 4096, INPUT + size - 256, INPUT - 256):
         assert ask(out_at=out_at) == separate
     assert ask(out_at=WORKSPACE) == ask(in_at=WORKSPACE) == separate
+
+
+@pytest.mark.parametrize("C,K,H", [(512, 256, 3), (512, 512, 10), (448, 256, 4)])
+def test_a_pointwise_layer_that_splits_its_depth_keeps_its_launch(model_launches, C, K, H):  # noqa: F811
+    layers = straight(("dw", C, 1), ("conv", C, K, 1, 1, 0))
+    assert model_launches(256, 1, (C, H, H), layers) == [("dwpw", 2)]
+    assert model_launches(256, 1, (C, H, H), layers, split_k=8) == [("dwconv", 1), ("conv", 1)]
