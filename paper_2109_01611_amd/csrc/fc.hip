@@ -55,8 +55,9 @@ __device__ __forceinline__ uint4 load_chunk(const __bf16 *row_ptr, int k, int In
 
 // NB = batch tiles of 16 rows handled per workgroup (1 or 2); NW = wavefronts
 // that split the In range (4, or 16 for long rows so that enough loads are in
-// flight per CU to keep HBM busy).
-template <int NB, int NW, bool VEC>
+// flight per CU to keep HBM busy).  DEEP: an instance with the LONG steps below; it takes 144 or 210 registers
+// where the plain one takes 46 or 64.
+template <int NB, int NW, bool VEC, bool DEEP>
 __global__ __launch_bounds__(NW * 64) void fc_kernel(const FcParams p) {
     __shared__ float red[NW - 1][NB][64][4];
 
@@ -83,14 +84,12 @@ __global__ __launch_bounds__(NW * 64) void fc_kernel(const FcParams p) {
     const int s_begin = wave * per_wave;
     const int s_end = min(steps, s_begin + per_wave);
 
-    // requested here: behind the sums its latency would stand in front of the stores
-    const float bias = (p.b && o_ok) ? p.b[o] : 0.f;
     f32x4 acc[NB];
 #pragma unroll
     for (int t = 0; t < NB; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     int s = s_begin;
-    if constexpr (VEC && NW == 4) {   // 16 wavefronts have no registers for it
+    if constexpr (DEEP) {
         // Whole steps, LONG at a time and without a test: a row that does not exist reads row 0, and only its own
         // outputs, which nobody stores, depend on it.
         for (; s + LONG <= min(s_end, p.In / 32); s += LONG) {
@@ -128,6 +127,8 @@ __global__ __launch_bounds__(NW * 64) void fc_kernel(const FcParams p) {
                                                                  acc[t], 0, 0, 0);
     }
 
+    // requested here: behind the barrier its latency would stand in front of the stores
+    const float bias = (p.b && o_ok) ? p.b[o] : 0.f;
     if (wave > 0) {
 #pragma unroll
         for (int t = 0; t < NB; ++t)
@@ -203,9 +204,6 @@ __global__ __launch_bounds__(1024) void fc_split_kernel(const FcParams p, float 
     const int s_begin = r_begin + wave * per_wave;
     const int s_end = min(r_end, s_begin + per_wave);
 
-    float bias[OB];   // requested early, as above
-#pragma unroll
-    for (int j = 0; j < OB; ++j) bias[j] = p.b && o_ok[j] ? p.b[o0 + j * 16 + sub] : 0.f;
     f32x4 acc[NB][OB];
 #pragma unroll
     for (int t = 0; t < NB; ++t)
@@ -234,6 +232,11 @@ __global__ __launch_bounds__(1024) void fc_split_kernel(const FcParams p, float 
                                                                          acc[t][j], 0, 0, 0);
     }
 
+    // Requested in front of the barrier, as above, although it costs a spilled register: over 60 shapes (8192 to 25088
+    // features, batch 1 to 32, 64 to 256 CUs) 4 % faster than behind the sums, up to 10 % at batch 32.
+    float bias[OB];
+#pragma unroll
+    for (int j = 0; j < OB; ++j) bias[j] = p.b && o_ok[j] ? p.b[o0 + j * 16 + sub] : 0.f;
     if (wave > 0) {
 #pragma unroll
         for (int t = 0; t < NB; ++t)
@@ -382,7 +385,21 @@ __global__ void zero_counters_kernel(unsigned *cnt, int n) {
     if (i < n) cnt[i] = 0u;
 }
 
+// Workgroups of fc_kernel: 16 outputs by 16 or 32 batch rows each.
+dim3 fc_grid(int N, int Out) {
+    return dim3(static_cast<unsigned>((Out + 15) / 16), N <= 16 ? 1u : static_cast<unsigned>((N + 31) / 32));
+}
+
 }  // namespace
+
+// Rows with LONG steps and more for each of the four wavefronts, in layers of up to two workgroups per CU: beyond that
+// the registers cost more wavefronts than the requests in flight are worth (us, plain and deep: 2048 -> 1000 at batch 256
+// on 256 CUs 14.7 and 14.3, at batch 512 24.9 and 26.1, at batch 1024 45.8 and 49.6; 64 -> 4096, which has no such steps
+// but ran in that instance, at batch 1024 12.3 and 29.7).
+bool fc_deep(int N, int In, int Out, int n_cu) {
+    const dim3 g = fc_grid(N, Out);
+    return In >= LONG * 4 * 32 && In < kFcLongRow && 1LL * g.x * g.y <= 2LL * (n_cu < 1 ? 1 : n_cu);
+}
 
 hipError_t launch_fc(const void *x, const void *w, const float *b, void *y, int N, int In, int Out,
                      int relu, int out_fp32, const LaunchCtx &ctx, hipStream_t stream) {
@@ -412,17 +429,17 @@ hipError_t launch_fc(const void *x, const void *w, const float *b, void *y, int 
 #undef GPULET_FC_SPLIT
         return hipGetLastError();
     }
-    const unsigned gx = static_cast<unsigned>((Out + 15) / 16);
-    const dim3 grid(gx, N <= 16 ? 1u : static_cast<unsigned>((N + 31) / 32));
-#define GPULET_FC_LAUNCH(NB, NW, V) \
-    hipLaunchKernelGGL((fc_kernel<NB, NW, V>), grid, dim3(NW * 64), 0, stream, p)
-    if (N <= 16) {
-        if (wide) { if (vec) GPULET_FC_LAUNCH(1, 16, true); else GPULET_FC_LAUNCH(1, 16, false); }
-        else { if (vec) GPULET_FC_LAUNCH(1, 4, true); else GPULET_FC_LAUNCH(1, 4, false); }
-    } else {
-        if (wide) { if (vec) GPULET_FC_LAUNCH(2, 16, true); else GPULET_FC_LAUNCH(2, 16, false); }
-        else { if (vec) GPULET_FC_LAUNCH(2, 4, true); else GPULET_FC_LAUNCH(2, 4, false); }
-    }
+    const dim3 grid = fc_grid(N, Out);
+    const bool deep = vec && fc_deep(N, In, Out, ctx.n_cu);
+#define GPULET_FC_LAUNCH(NB, NW, V, D) \
+    hipLaunchKernelGGL((fc_kernel<NB, NW, V, D>), grid, dim3(NW * 64), 0, stream, p)
+#define GPULET_FC_ROWS(NB) \
+    if (wide) { if (vec) GPULET_FC_LAUNCH(NB, 16, true, false); else GPULET_FC_LAUNCH(NB, 16, false, false); } \
+    else if (deep) GPULET_FC_LAUNCH(NB, 4, true, true); \
+    else if (vec) GPULET_FC_LAUNCH(NB, 4, true, false); \
+    else GPULET_FC_LAUNCH(NB, 4, false, false)
+    if (N <= 16) { GPULET_FC_ROWS(1); } else { GPULET_FC_ROWS(2); }
+#undef GPULET_FC_ROWS
 #undef GPULET_FC_LAUNCH
     return hipGetLastError();
 }

@@ -126,6 +126,8 @@ void set_conv_split_k(int max_split);
 hipError_t launch_pool(const void *x, void *y, int N, int C, int H, int W, int P, int Q, int mode,
                        int k, int stride, int pad, hipStream_t stream);
 constexpr int kFcLongRow = 8192;   // rows from here on are split over 16 wavefronts and more (fc.hip), below over four
+// Whether a layer with 16-byte rows runs in the instance that holds 16 depth steps in flight.
+bool fc_deep(int N, int In, int Out, int n_cu);
 hipError_t launch_fc(const void *x, const void *w, const float *b, void *y, int N, int In, int Out,
                      int relu, int out_fp32, const LaunchCtx &ctx, hipStream_t stream);
 // The layer with its scratch in the library's static device array (no allocation anywhere);

@@ -39,8 +39,9 @@ hipError_t launch_dwconv(const void *, const void *, const float *, void *, int,
                          hipStream_t) {
     return say("dwconv", 1);
 }
-hipError_t launch_fc(const void *, const void *, const float *, void *, int, int, int, int, int, const LaunchCtx &, hipStream_t) {
-    return say("fc", 1);
+hipError_t launch_fc(const void *, const void *, const float *, void *, int N, int In, int Out, int, int, const LaunchCtx &c,
+                     hipStream_t) {
+    return say(fc_deep(N, In, Out, c.n_cu) ? "fc-deep" : "fc", 1);
 }
 hipError_t launch_image_chain(const ChainLayer *, int n, const void *, int, hipStream_t) { return say("chain", n); }
 hipError_t launch_dwpw(const DwPwArgs &, int, hipStream_t) { return say("dwpw", 2); }

@@ -916,7 +916,9 @@ def test_conv_timeline_records_stamps_for_the_small_patch_tiles(part, case):
 FC_CASES = [(32, 400, 120), (32, 120, 84), (32, 84, 10), (1, 2048, 1000), (8, 1024, 1000),
             (33, 72, 17), (5, 8, 3), (40, 4096, 1000), (16, 25088, 64), (2, 100, 7),
             # long rows: 64 outputs per workgroup, depth split over workgroups
-            (32, 25088, 136), (1, 25088, 256), (17, 8192, 4096), (3, 8195, 20), (40, 9000, 72)]
+            (32, 25088, 136), (1, 25088, 256), (17, 8192, 4096), (3, 8195, 20), (40, 9000, 72),
+            # 16 depth steps in flight, then a remainder that ends in a partial step; too many workgroups for that
+            (1, 2056, 1000), (33, 4104, 72), (8, 2048, 8400)]
 
 
 @pytest.mark.parametrize("case", FC_CASES, ids=lambda c: "x".join(map(str, c)))
