@@ -167,6 +167,12 @@ double tall_cost(const ConvParams &p, int th, int tw, double geo, int n_cu) {
     return static_cast<double>((tall_tiles(p, th, tw) + n_cu - 1) / n_cu) * 224 * 128 / eff;
 }
 
+// Loading 144 registers of weights per consumer (about 2.5 us) wants three pixel tiles per workgroup, and 4.5 where several
+// filter tiles share a gathered pixel tile.
+bool c64_enough_tiles(const C64Grid &g, int n_cu) {
+    return 2LL * g.tiles_m >= (g.tiles_n == 1 ? 6LL : 9LL) * std::max(1, n_cu / g.tiles_n);
+}
+
 Choice choose_kernel(const ConvParams &p, bool vec, const LaunchCtx &ctx) {
     // Pick the tile and the split of the depth that minimise
     //   (work items on the busiest CU) x (tile area) x (share of the depth + fixed cost of a split) / efficiency.
@@ -249,16 +255,18 @@ Choice choose_kernel(const ConvParams &p, bool vec, const LaunchCtx &ctx) {
     int tw64 = 0;
     const bool c64_ok = c64_applicable(p, vec, &tw64);
     if (best == 10 && !c64_ok) best = 1;
-    // Loading 144 registers of weights per consumer (about 2.5 us) pays from three pixel tiles per workgroup on
-    // where one filter tile covers the layer: 3x3 64 -> 64 on 56x56 at batch 32 16.3 -> 15.6 us, at batch 16 on 128 CUs
-    // 14.1 -> 13.3 (two tiles: 8.1 and 8.9); with several filter tiles, which share a gathered pixel tile, later: 64 ->
-    // 192 on 56x56 at batch 8 on 128 CUs (4.7 tiles) 17.3 -> 16.1, 64 -> 128 on 112x112 at batch 4 (3 tiles) 13.2 and 15.2.
+    // The resident-weight kernel takes 4.2 us and 2.1 to 2.4 per pixel tile of its busiest workgroup, the best gathering
+    // tile 2.4 us and 2.0 to 2.2 per 128x64 of the cost above.  In 1454 layers (8 to 320 filters, maps of 14 to 224, batch
+    // 1 to 64, 64 to 256 CUs) the second condition picks the slower one in nine, by 4 % at most: 64 -> 64 on 56x56 at batch 32 on
+    // 256 CUs (4 tiles) 15.0 us gathered and 14.3, 64 -> 192 there (10 tiles) 34.3 and 27.8, but 64 -> 128 on 64 CUs
+    // (25 tiles) 53.6 and 57.7, 64 -> 256 on 20x20 on 128 CUs (columns of 16 in rows of 20, 5 tiles) 11.3 and 15.7.
+    // The tiles' efficiencies hold for long depths: at nine slices those over 64 rows x 128 filters are 8 % dearer, and 128x128
+    // is 5 % cheaper unless all CUs draw on memory.
     if (forced < 0 && c64_ok) {
-        const int n_cb = (p.Q + tw64 - 1) / tw64;
-        const long long tiles_m = ((1LL * p.N * p.P * tw64 + PATCH_BM - 1) / PATCH_BM) * n_cb;
-        const int tiles_n = (p.K + 63) / 64;
-        const int wgs_per_col = std::max(1, n_cu / tiles_n);
-        if (2 * tiles_m >= (tiles_n == 1 ? 6LL : 9LL) * wgs_per_col) best = 10;
+        const C64Grid g = c64_grid(p, tw64, n_cu);
+        const bool large = best == 6 || best == 12 || best == 13;
+        const double nine = large ? 1.08 : best == 0 && n_cu <= 192 ? 0.95 : 1.0;
+        if (c64_enough_tiles(g, n_cu) && (g.rounds + 1.0) * PATCH_BM * 64 <= nine * best_cost) best = 10;
     }
     if (best == 9 && !stem_applicable(p)) best = 1;
     if (forced < 0 && stem_applicable(p)) best = 9;  // by shape alone: the same bits in every batch and gpu-let
@@ -330,6 +338,12 @@ bool conv_pool2_fusable(const ConvArgs &a, const LaunchCtx &ctx) {
     const Choice c = choose_kernel(p, vec, ctx);
     if (splits_depth(c)) return false;   // partial sums: other bits than the pooled epilogue's
     if (c.best == 10) return c64_applicable(p, vec, &tw, true);   // the same kernel with another epilogue
+    // With the pool it also pays where it does not alone: in 343 pairs (16 to 256 filters, maps of 14 to 224, batch 1 to
+    // 64, 64 to 256 CUs) by 7 % at least.
+    if (c64_applicable(p, vec, &tw, true)) {
+        const int n_cu = std::max(1, ctx.n_cu);
+        return c64_enough_tiles(c64_grid(p, tw, n_cu), n_cu);
+    }
     if (p.C < 2 * BK || !tall_eligible(p, vec, &th, &tw, &geo, true)) return false;
     if (c.cost <= 0.0) return false;
     return tall_cost(p, th, tw, geo, ctx.n_cu < 1 ? 1 : ctx.n_cu) <= 1.15 * c.cost;

@@ -400,6 +400,11 @@ bool patch_eligible(const ConvParams &p, bool vec, int *tw_out);
 int patch_variant(const ConvParams &p, int tw, int n_cu, bool *one_round);
 hipError_t launch_patch(ConvParams p, int tw, int variant, hipStream_t stream);
 bool c64_applicable(const ConvParams &p, bool vec, int *tw_out, bool pool2 = false);
+// Its grid on n_cu CUs: pixel tiles, filter tiles, workgroups per filter tile, and the pixel tiles the busiest workgroup walks.
+struct C64Grid {
+    int tiles_m, tiles_n, wgs_per_col, die_aware, rounds;
+};
+C64Grid c64_grid(const ConvParams &p, int tw, int n_cu);
 hipError_t launch_c64(ConvParams p, int tw, int n_cu, bool pool2, hipStream_t stream);
 
 // conv_tall.hip: tile 11 (3x3, 224 x 128 tile, input patch in LDS, one tap per ring step).

@@ -682,26 +682,36 @@ bool c64_applicable(const ConvParams &p, bool vec, int *tw_out, bool pool2) {
     return !pool2 || (p.relu && p.P % 2 == 0 && p.Q % 2 == 0 && tw >= 2 && tw <= 32 && (tw & (tw - 1)) == 0);
 }
 
+// One workgroup per CU (registers), all resident at once; a multiple of 8 per filter tile where possible, so that every
+// die can own a contiguous eighth of the pixel tiles.
+C64Grid c64_grid(const ConvParams &p, int tw, int n_cu) {
+    C64Grid g;
+    const long long lin = 1LL * p.N * p.P * tw;
+    g.tiles_m = static_cast<int>((lin + PATCH_BM - 1) / PATCH_BM) * ((p.Q + tw - 1) / tw);
+    g.tiles_n = (p.K + 63) / 64;
+    g.wgs_per_col = std::max(1, std::min(g.tiles_m, n_cu / g.tiles_n));
+    g.die_aware = g.wgs_per_col >= 8 ? 1 : 0;
+    if (g.die_aware) g.wgs_per_col &= ~7;
+    const int dies = g.die_aware ? 8 : 1, per_die = (g.tiles_m + dies - 1) / dies, wgs = g.wgs_per_col / dies;
+    g.rounds = (per_die + wgs - 1) / wgs;
+    return g;
+}
+
 hipError_t launch_c64(ConvParams p, int tw, int n_cu, bool pool2, hipStream_t stream) {
     p.pool2 = pool2 ? 2 : 0;
     p.th = 0;
     while (pool2 && (2 << p.th) < tw) ++p.th;   // log2(tw / 2)
+    const C64Grid g = c64_grid(p, tw, n_cu);
+    const int wgs_per_col = g.wgs_per_col, tiles_m = g.tiles_m, die_aware = g.die_aware;
     p.tw = tw;
     p.n_cb = (p.Q + tw - 1) / tw;
-    const long long lin = 1LL * p.N * p.P * tw;
-    const int tiles_m = static_cast<int>((lin + PATCH_BM - 1) / PATCH_BM) * p.n_cb;
-    p.tiles_n = (p.K + 63) / 64;
+    p.tiles_n = g.tiles_n;
     p.n_tiles = tiles_m * p.tiles_n;
     p.split_k = 1;
     p.d_tw = make_fastdiv(tw);
     p.d_ncb = make_fastdiv(p.n_cb);
     p.d_pwt = make_fastdiv(tw + 2);
     p.d_hp = make_fastdiv(p.H + 2 * p.pad);
-    // one workgroup per CU (registers), all resident at once; a multiple of 8 per filter tile
-    // where possible, so that every die can own a contiguous eighth of the pixel tiles
-    int wgs_per_col = std::max(1, std::min(tiles_m, n_cu / p.tiles_n));
-    const int die_aware = wgs_per_col >= 8 ? 1 : 0;
-    if (die_aware) wgs_per_col &= ~7;
     if (p.stamps)
         hipLaunchKernelGGL(conv3x3_c64_kernel<true>, dim3(static_cast<unsigned>(wgs_per_col * p.tiles_n)), dim3(512), 0, stream, p,
                            wgs_per_col, tiles_m, die_aware);
