@@ -314,10 +314,14 @@ hipError_t launch_conv(const ConvArgs &a, const LaunchCtx &ctx, hipStream_t stre
             // at about 60 KB/us, however many of them it has requested (a ring of 8 stages instead of 3 made 32x32
             // tiles 2 % slower), so what counts is how many CUs share the operands' transfer.  1x1 2048 -> 512 on 7x7 at
             // batch 1 4.6 us in 32x32, 3x3/2 512 -> 512 on 14x14 9.0 and 7.8, 3x3/2 256 -> 256 on 28x28 6.0 and 5.4;
-            // with a second workgroup on a CU they lose.
+            // with a second workgroup on a CU they lose.  Filters larger than 1x1 on other channel counts than multiples of
+            // 64, whose producers work out every chunk's tap, have two producers for it instead of four and lose
+            // too until the depth is long (3x3/2 8 -> 24 on 14x14 4.7 and 7.0, 5x5 16 -> 96 5.4 and 5.9; 388 such layers
+            // of fewer than 28 slices 14 % slower, the other 1112 measured 6 % faster).
             int tile = c.best;
             const long long tiles16 = 1LL * ((p.M + 15) / 16) * ((p.K + 15) / 16);
-            if (tile == 14 && vec && c.split == 1 && g_tile_override.load() < 0 && tiles16 <= n_cu) tile = kTile16;
+            const bool plain = p.R * p.S == 1 || p.C % BK == 0 || p.Kg >= 28 * BK;
+            if (tile == 14 && vec && c.split == 1 && g_tile_override.load() < 0 && plain && tiles16 <= n_cu) tile = kTile16;
             return launch_igemm(p, vec, tile, c.split, tiles128 > n_cu, stream);
         }
     }
