@@ -168,22 +168,12 @@ __global__ __launch_bounds__(256) void pool_global_avg_vec8(const PoolParams p) 
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = 0.f;
     if (c8 < cv) {
-        // FLY pixels requested before the first is added: one memory latency instead of one per pixel (7x7 of 2048
-        // channels at batch 1 GAVG us).  Same order of additions.
-        constexpr int FLY = 8;
-        for (int i0 = slice; i0 < hw; i0 += 8 * FLY) {
-            uint4 v[FLY];
+        for (int i = slice; i < hw; i += 8) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(p.x + ((n * hw + i) * p.C + c8 * 8));
+            float f[8];
+            unpack8(v, f);
 #pragma unroll
-            for (int u = 0; u < FLY; ++u)
-                v[u] = *reinterpret_cast<const uint4 *>(p.x + ((n * hw + min(i0 + 8 * u, hw - 1)) * p.C + c8 * 8));
-#pragma unroll
-            for (int u = 0; u < FLY; ++u) {
-                if (i0 + 8 * u >= hw) break;
-                float f[8];
-                unpack8(v[u], f);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) acc[j] += f[j];
-            }
+            for (int j = 0; j < 8; ++j) acc[j] += f[j];
         }
     }
 #pragma unroll
