@@ -390,7 +390,10 @@ bool dwpw_applicable(const DwPwArgs &a, int n_cu) {
     if (r.bn == 0) return false;
     // Against two launches (us, two and one):
     // 32 channels, 150x150: 9.3/7.7 at batch 1 on 160 CUs, 16.1/11.1 at batch 4 on 256 (all workgroups resident); with more
-    // rounds the pair alone gains (52/47 at batch 32) and whole SSD-MobileNet loses (435 and 442 us).
+    // rounds the pair alone gains (52/47 at batch 32) and whole SSD-MobileNet loses (435 and 442 us).  Its launch takes 7.2 us
+    // however small, the two together 5.5 to 7.9 below one workgroup for three CUs (102 of 119 pairs 3 % slower and
+    // more, 7 % in the mean), and several workgroups per tile want one round (128 filters: 8.5/7.8 with 0.96 workgroups per
+    // CU, 9.9/10.0 with 1.2); between these lines 52 pairs gain 4.5 % in the mean.
     // 128 channels, 75x75: 8.0/6.8 at batch 1, 37.2/35.9 at batch 32 on 256 CUs (11 tiles per CU); on 64 CUs at batch 16
     // (23 per CU) 60.7/61.4.  With two workgroups per tile, each doing the depthwise part (38x38 to 256): 8.5/7.1 at
     // batch 4 (0.75 workgroups per CU), 9.3/9.2 at batch 8, 12.7/14.2 at batch 16.
@@ -398,8 +401,9 @@ bool dwpw_applicable(const DwPwArgs &a, int n_cu) {
     // 512 on 19x19 8.2/7.6 and 10.4/9.5 at batch 1 and 8, where a workgroup has one pass over the filters, 12.8/13.1 at
     // batch 16 with two.  One workgroup fills a CU, so a second round costs as much as the first.
     if (r.deep) return r.passes == 1 && r.tiles * r.n_split <= cus;
-    if (r.n_split > 1) return 4 * r.tiles * r.n_split <= 5LL * cus;
-    return r.tiles <= (a.C == 32 ? 4LL : 14LL) * cus;
+    const long long wgs = r.tiles * r.n_split;
+    if (a.C == 32) return 3 * wgs >= cus && wgs <= (r.n_split > 1 ? 1LL : 4LL) * cus;
+    return r.n_split > 1 ? 4 * wgs <= 5LL * cus : wgs <= 14LL * cus;
 }
 
 hipError_t launch_dwpw(const DwPwArgs &a, int n_cu, hipStream_t stream) {

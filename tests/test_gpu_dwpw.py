@@ -22,14 +22,16 @@ def _pair(C, H, W, K, relu=True, stride=1):
 # C, H, W, K, batch, percent: odd maps, maps smaller than a block, tiles that span images, a ragged last tile, several
 # workgroups per tile, both widths of filter tiles and heights of pixel tiles of the deep kernel
 CASES = [
-    (32, 21, 18, 64, 3, 100), (32, 1, 1, 64, 1, 100), (32, 9, 50, 128, 2, 100), (32, 40, 37, 64, 30, 25),
+    (32, 21, 18, 64, 19, 25), (32, 1, 1, 64, 1024, 25), (32, 9, 50, 128, 8, 25), (32, 40, 37, 64, 30, 25),
     (128, 9, 11, 128, 4, 100), (128, 10, 10, 384, 3, 100), (128, 30, 31, 128, 8, 20),
     (192, 7, 5, 128, 2, 100), (192, 28, 28, 128, 8, 60), (256, 9, 9, 256, 3, 100), (256, 38, 38, 256, 8, 100),
     (320, 5, 6, 384, 2, 100), (512, 19, 19, 512, 1, 60), (512, 19, 19, 512, 8, 100), (512, 3, 2, 256, 1, 100),
     (512, 10, 10, 1024, 16, 100), (256, 18, 19, 256, 6, 25),
 ]
-# two launches: stride 2, other channel counts, more than one round of the deep kernel, filters no multiple of a tile
+# two launches: stride 2, other channel counts, more than one round of the deep kernel, filters no multiple of a tile, 32 channels
+# on few workgroups
 SEPARATE = [
+    (32, 21, 18, 64, 3, 100, 1), (32, 1, 1, 64, 1, 100, 1), (32, 9, 50, 128, 2, 100, 1),
     (32, 21, 18, 64, 3, 100, 2), (64, 14, 9, 128, 3, 100, 1), (1024, 5, 5, 1024, 1, 100, 1), (512, 19, 19, 512, 32, 100, 1),
     (128, 9, 11, 72, 1, 100, 1), (32, 9, 11, 96, 1, 100, 1), (40, 9, 11, 64, 1, 100, 1), (128, 75, 75, 128, 16, 20, 1),
 ]

@@ -39,3 +39,13 @@ def test_a_pointwise_layer_that_splits_its_depth_keeps_its_launch(model_launches
     layers = straight(("dw", C, 1), ("conv", C, K, 1, 1, 0))
     assert model_launches(256, 1, (C, H, H), layers) == [("dwpw", 2)]
     assert model_launches(256, 1, (C, H, H), layers, split_k=8) == [("dwconv", 1), ("conv", 1)]
+
+
+@pytest.mark.parametrize("cu,N,H,W,K,shared", [
+    (256, 1, 150, 150, 64, True), (256, 4, 150, 150, 64, True), (256, 32, 150, 150, 64, False),
+    (256, 3, 21, 18, 64, False), (256, 1, 38, 38, 64, False), (64, 8, 9, 50, 128, True), (64, 2, 9, 50, 128, False),
+    (128, 3, 56, 56, 256, False),
+])
+def test_depthwise_pairs_of_32_channels(model_launches, cu, N, H, W, K, shared):  # noqa: F811
+    layers = straight(("dw", 32, 1), ("conv", 32, K, 1, 1, 0))
+    assert model_launches(cu, N, (32, H, W), layers) == ([("dwpw", 2)] if shared else [("dwconv", 1), ("conv", 1)])
