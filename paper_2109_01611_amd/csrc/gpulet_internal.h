@@ -151,6 +151,8 @@ struct ChainLayer {
 };
 // Whether l[0 .. n) can run so (n >= 2); x and the destinations of convolutions and pools are 16-byte aligned.
 bool image_chain_applicable(const ChainLayer *l, int n);
+// Whether that is the faster way for N images on n_cu CUs.
+bool image_chain_pays(const ChainLayer *l, int n, int N, int n_cu);
 hipError_t launch_image_chain(const ChainLayer *l, int n, const void *x, int N, hipStream_t stream);
 
 // conv_dwpw.hip: a depthwise 3x3 / pad 1 convolution (stride 1 or 2, C channels, H x W -> P x Q) and the 1x1

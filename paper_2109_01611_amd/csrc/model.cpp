@@ -519,7 +519,7 @@ hipError_t enqueue(const Bound &bd, gpulet_partition *p) {
                 for (size_t t = k + 1; t < n; ++t) taken = taken || steps[i + t].out_buf == sk.out_buf;
                 l[k].y = taken ? nullptr : bd.ptr(sk.out_buf);
             }
-            if (chain_aligned(l, n, bd.ptr(s.in_buf))) {
+            if (chain_aligned(l, n, bd.ptr(s.in_buf)) && image_chain_pays(l, static_cast<int>(n), bd.batch, ctx.n_cu)) {
                 e = launch_image_chain(l, static_cast<int>(n), bd.ptr(s.in_buf), bd.batch, stream);
                 if (e != hipSuccess) return e;
                 p->kernels_enqueued.fetch_add(1);

@@ -42,7 +42,8 @@ def _long_row(W):
     # 8 x 32 x W / 2 features: from 8192 on the fully connected kernel adds in another order
     return Model("row%d" % W, (8, 64, W), "normal", [
         _maxpool("a", "x", "ta", 2, 2, 0),
-        _fc("b", "ta", "y", 8 * 32 * (W // 2), 4, False),
+        _fc("b", "ta", "tb", 8 * 32 * (W // 2), 4, True),
+        _fc("c", "tb", "y", 4, 2, False),
     ], "y")
 
 
@@ -50,7 +51,7 @@ def _long_row(W):
 @pytest.mark.parametrize("model,batch,pct,launches", [
     (workloads.lenet5(), 1, 100, 1), (workloads.lenet5(), 32, 20, 1), (workloads.lenet5(), 300, 60, 1),
     (_mixed(), 3, 40, 2), (_ends_in_a_map(), 2, 100, 1),
-    (_long_row(62), 3, 100, 1), (_long_row(64), 3, 100, 2)], ids=lambda v: getattr(v, "name", str(v)))
+    (_long_row(62), 3, 100, 1), (_long_row(64), 3, 100, 3)], ids=lambda v: getattr(v, "name", str(v)))
 def test_layers_of_one_launch_leave_what_separate_launches_leave(model, batch, pct, launches, reuse):
     params = workloads.parameters(model, 3)
     x = workloads.batch_input(model, batch, 3)
