@@ -499,27 +499,28 @@ bool chain_params(const ChainLayer *l, int n, ChainParams &c) {
     return true;
 }
 
-// Estimated time (us) of the run in one launch, and of its layers one by one.  Fitted to 900 runs of two to seven
-// layers (8 to 256 channels on 4x4 to 40x40, 64 to 4096 features, batch 1 to 2048, 64 to 256 CUs); they miss the
-// measured times by 8 and 12 % (standard deviation).
+// Estimated time (us) of the run in one launch, and of its layers one by one.  Fitted to 1600 runs of two to seven
+// layers (8 to 256 channels on 4x4 to 40x40, 64 to 2048 features, batch 1 to 2048, 64 to 256 CUs); they miss the
+// measured times by 7 and 12 % (standard deviation).
 double together_us(const ChainLayer *l, int n, int N, int n_cu) {
     auto up = [](double a, double b) { return std::ceil(a / b); };
     const double in_kb = 2.0 * l[0].C * l[0].H * l[0].W / 1024;
-    double image = 3.2 + 0.0127 * in_kb, kb = in_kb;   // arguments, staging, the first barrier
+    double image = 3.1 + 0.0082 * in_kb, kb = in_kb;   // arguments, staging, the first barrier
     for (int i = 0; i < n; ++i) {
         const ChainLayer &s = l[i];
         const double cols = up(s.K, 16), out_kb = 2.0 * s.K * s.P * s.Q / 1024;
-        image += 0.76 + 0.052 * out_kb;
+        image += 0.79 + 0.053 * out_kb;
         if (s.kind == GPULET_OP_CONV) {
-            image += cols * (0.0485 * up(1.0 * s.R * s.S * s.C, 32) + 0.134 * up(up(1.0 * s.P * s.Q, 16), kWaves));
+            const int depth = s.R * s.S * s.C;   // a multiple of 128: all filters start in the same banks
+            image += cols * ((depth % 128 == 0 ? 0.056 : 0.034) * up(depth, 32) + 0.15 * up(up(1.0 * s.P * s.Q, 16), kWaves));
         } else if (s.kind == GPULET_OP_FC) {
             const double in = 1.0 * s.C * s.H * s.W;
-            image += 0.35 * up(4 * cols, kWaves) * up(up(up(in, 32), 4), kFcSteps) + 0.0139 * 2 * in * s.K / 1024;
+            image += 0.33 * up(4 * cols, kWaves) * up(up(up(in, 32), 4), kFcSteps) + 0.015 * 2 * in * s.K / 1024;
         }
         kb += out_kb;
     }
     // one image per CU at a time; the next one's arguments and first loads overlap the last one's stores
-    return image * (0.2 + 0.8 * up(N, n_cu)) + 0.055 * N * kb / 1024;
+    return image * (0.2 + 0.8 * up(N, n_cu)) + 0.066 * N * kb / 1024;
 }
 
 double separate_us(const ChainLayer *l, int n, int N, int n_cu) {
@@ -530,13 +531,13 @@ double separate_us(const ChainLayer *l, int n, int N, int n_cu) {
         const double out = 1.0 * s.K * s.P * s.Q, in = 1.0 * s.C * s.H * s.W;
         if (s.kind == GPULET_OP_CONV) {
             const bool plain = s.R * s.S == 1 || s.C % BK == 0;
-            us += 2.9 + 0.2 * up(1.0 * s.R * s.S * s.C, BK) + (plain ? 0.92 : 1.8) * N * s.P * s.Q * up(s.K, 64) / 128 / n_cu +
-                  0.0112 * N * 2 * (in + out) / 1024 / n_cu;
+            us += 2.9 + 0.19 * up(1.0 * s.R * s.S * s.C, BK) + (plain ? 0.98 : 1.87) * N * s.P * s.Q * up(s.K, 64) / 128 / n_cu +
+                  0.0106 * N * 2 * (in + out) / 1024 / n_cu;
         } else if (s.kind == GPULET_OP_POOL) {
-            us += 2.7 + 0.0112 * N * 2 * out * (s.R * s.S + 1) / 1024 / n_cu;
+            us += 2.7 + 0.0106 * N * 2 * out * (s.R * s.S + 1) / 1024 / n_cu;
         } else {
             const double steps = up(in, 32) / 4;
-            us += 2.9 + 0.12 * steps + 0.35 * up(N, 32) * up(s.K, 16) * steps / n_cu;
+            us += 2.9 + 0.1 * steps + 0.36 * up(N, 32) * up(s.K, 16) * steps / n_cu;
         }
     }
     return us;
@@ -547,12 +548,12 @@ double separate_us(const ChainLayer *l, int n, int N, int n_cu) {
 // A workgroup takes its image through the run alone, on one CU: few and small layers win by the launches they
 // save, and by what separate kernels of many images waste on 8 channels; wide layers, short runs and several images per
 // CU lose (LeNet-5 wins at every batch, batch 2048 186 and 96 us; 1x1 256 -> 64 -> 256 on 7x7 at batch 1 7.3 and 13.7,
-// at batch 2048 30 and 102; 256 -> 256 -> 32 features at batch 2048 10.6 and 60).  With this line 294 of 556 runs share a
-// launch and five of those are 3 % slower or more, 1 % above always taking the faster way; sharing all of them was 11 % slower
-// than sharing none.
+// at batch 2048 30 and 102; 256 -> 256 -> 32 features at batch 2048 10.6 and 60).  Of the runs above 991 fit as a whole:
+// with this line 565 share a launch, a third faster in the mean (17 of them 3 % slower and more), 0.7 % above always
+// taking the faster way; sharing all of them is 10 % slower than sharing none.
 bool image_chain_pays(const ChainLayer *l, int n, int N, int n_cu) {
     const int cus = n_cu < 1 ? 1 : n_cu;
-    return together_us(l, n, N, cus) <= 0.92 * separate_us(l, n, N, cus);
+    return together_us(l, n, N, cus) <= 0.95 * separate_us(l, n, N, cus);
 }
 
 bool image_chain_applicable(const ChainLayer *l, int n) {
