@@ -9,6 +9,8 @@ import pytest
 
 from paper_2109_01611_amd import gpulet, lowering, workloads
 
+from model_launches import model_launches, straight  # noqa: F401  (fixture)
+
 
 def _lower(model, **kw):
     return lowering.DeviceModel(model, workloads.parameters(model, 3), "cpu", **kw)
@@ -126,3 +128,29 @@ def test_a_convolutions_input_outlives_the_max_pool_behind_it():
                 pairs += 1
                 assert b.out_buf != a.in_buf, (a.in_buf, a.out_buf, b.out_buf)
         assert pairs == (5 if model.name.startswith("vgg") else 2)
+
+
+def _pair_buffers(C, K, k=1, stride=1, residual=None):
+    """(input, output) buffer of a depthwise 3x3 + 1x1 pair inside a model, and its layers."""
+    model = workloads.Model("pair", (8, 20, 20), "normal", [
+        workloads._conv("a", "x", "t", 8, C, 1, 1, 0, True),
+        workloads._dwconv("d", "t", "u", C, 3, stride, 1, True),
+        workloads._conv("p", "u", "v", C, K, k, 1, k // 2, True, residual),
+        workloads._conv("z", "v", "y", K, 8, 1, 1, 0, True)], "y")
+    dm = _lower(model)
+    return dm.layers[1].in_buf, dm.layers[2].out_buf
+
+
+@pytest.mark.parametrize("C,K,stride", [(32, 64, 1), (32, 96, 1), (32, 128, 1), (32, 64, 2), (64, 128, 1), (128, 128, 1), (128, 192, 1),
+                                        (128, 384, 1), (192, 128, 1), (200, 128, 1), (256, 64, 1), (256, 256, 1), (256, 256, 2),
+                                        (448, 384, 1), (512, 512, 1), (576, 128, 1), (1024, 1024, 1)])
+def test_a_pair_keeps_its_input_only_where_it_may_be_one_launch(model_launches, C, K, stride):  # noqa: F811
+    layers = straight(("dw", C, stride), ("conv", C, K, 1, 1, 0))
+    shared = any(model_launches(cu, batch, (C, 20, 20), layers) == [("dwpw", 2)] for cu in (64, 256) for batch in (1, 4, 16))
+    in_buf, out_buf = _pair_buffers(C, K, stride=stride)
+    assert (in_buf != out_buf) == shared
+
+
+def test_ssd_workspace():
+    # the first pair's input is 46 MB of it (see lowering._may_share_launch); another 6 MB went with the pairs that never share
+    assert gpulet.model_workspace_bytes(_lower(workloads.ssd_mobilenet()).desc, 32) == 196505344
