@@ -141,10 +141,10 @@ __global__ __launch_bounds__(256) void conv_stem_kernel(const ConvParams p, cons
     fetch(cur, nxt);
     const float bias0 = tid < BN && p.b && n0 + tid < p.K ? p.b[n0 + tid] : 0.f;
 
-    // Weights -> LDS as [filter][r][s][4], zero where s >= S, c >= C or the filter does not exist.  All loads are
-    // issued before the first is used, behind those of the first patch: a workgroup starts with one memory
-    // latency.  (Eight 2-byte loads at a time were seven latencies: 7x7 on 224x224 at batch 1 9.0 us, now 5.7, at batch 32
-    // 25.5 and 22.4, on 128 CUs 37.7 and 34.1.)
+    // Weights -> LDS as [filter][r][s][4], zero where s >= S, c >= C or the filter does not exist.  Where four channels are
+    // stored, all loads are issued before the first is used, behind those of the first patch: a workgroup starts with one
+    // memory latency.  (Eight 2-byte loads at a time were seven latencies: 7x7 on 224x224 at batch 1 9.0 us, now 5.7, at
+    // batch 32 25.5 and 22.4, on 128 CUs 37.7 and 34.1.)
     unsigned short *wl = reinterpret_cast<unsigned short *>(stg_raw);
     if (p.C == 4 && (reinterpret_cast<uintptr_t>(p.w) & 7) == 0) {
         constexpr int WPX = WELEMS / 4, WPT = (WPX + 255) / 256;   // filter pixels of four channels
@@ -162,8 +162,12 @@ __global__ __launch_bounds__(256) void conv_stem_kernel(const ConvParams p, cons
         for (int u = 0; u < WPT; ++u)
             if (tid + u * 256 < WPX) *reinterpret_cast<uint2 *>(wl + (tid + u * 256) * 4) = v[u];
     } else {
-        constexpr int WPT = (WELEMS + 255) / 256, WB = WPT < 32 ? WPT : 32;
-#pragma unroll
+        // One to three channels: 2-byte loads, up to 16 per thread at a time (over 44 layers of 5x5 and 7x7, eight at a time
+        // take 1.4 % more in the mean and 32 2.3 %).  7x7 with up to 32 filters is mostly prologue, and its loads written
+        // out one by one cost more to fetch as code than they save: 16 filters on 28x24 at batch 2 6.6 us, in a loop 6.2.
+        constexpr int WPT = (WELEMS + 255) / 256, BATCHES = (WPT + 15) / 16, WB = (WPT + BATCHES - 1) / BATCHES;
+        constexpr int UNROLLED = R == 7 && NT == 1 ? 1 : BATCHES;
+#pragma unroll UNROLLED
         for (int i0 = 0; i0 < WPT; i0 += WB) {
             unsigned short v[WB];
 #pragma unroll

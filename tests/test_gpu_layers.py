@@ -560,6 +560,8 @@ STEM_CASES = [
     (1, 4, 20, 20, 72, 5, 1, 0),       # four channels, two filter tiles, second ragged; no padding
     (5, 2, 9, 130, 40, 7, 1, 3),       # wide and flat: five column tiles
     (1, 3, 5, 5, 8, 3, 1, 1),          # smaller than one tile
+    (2, 3, 29, 34, 16, 7, 2, 3),       # 7x7 with one 32-filter tile: the loads of its filters stay a loop
+    (1, 2, 40, 37, 32, 7, 1, 3),
 ]
 
 
