@@ -37,10 +37,13 @@ SEPARATE = [
 ]
 
 
-def _both_ways(model, batch, pct, fused_launches):
+def _both_ways(model, batch, pct, fused_launches, x=None, bias=True):
     dm = lowering.DeviceModel(model, workloads.parameters(model, 5), DEV)
+    if not bias:
+        for layer in dm.layers:
+            layer.b = None
     with gpulet.Partition(0, pct, 0) as p:
-        xd = dm.input_to_device(workloads.batch_input(model, batch, 5))
+        xd = dm.input_to_device(workloads.batch_input(model, batch, 5) if x is None else x)
         seen = []
         for fused in (False, True):
             gpulet.set_conv_pool_fusion(fused)
@@ -52,7 +55,9 @@ def _both_ways(model, batch, pct, fused_launches):
             finally:
                 gpulet.set_conv_pool_fusion(True)
             seen.append((y.clone(), dm.read_tensor("t", batch)))
-    assert torch.equal(seen[0][0], seen[1][0]) and torch.equal(seen[0][1], seen[1][1])
+    for a, b in zip(*seen):
+        assert torch.equal(a.isnan(), b.isnan()) and torch.equal(a.nan_to_num(nan=0.0), b.nan_to_num(nan=0.0))
+    return seen[1]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
@@ -60,6 +65,32 @@ def test_pair_in_one_launch_is_the_two_launches(case):
     C, H, W, K, batch, pct = case
     for relu in (True, False):
         _both_ways(_pair(C, H, W, K, relu), batch, pct, 1)
+
+
+# both kernels, both widths of filter tiles and heights of pixel tiles
+EDGES = [(32, 40, 37, 64, 30, 25), (128, 9, 11, 128, 8, 100), (256, 9, 9, 256, 6, 100), (256, 38, 38, 256, 8, 100)]
+
+
+@pytest.mark.parametrize("case", EDGES, ids=lambda c: "x".join(map(str, c)))
+def test_no_bias(case):
+    C, H, W, K, batch, pct = case
+    _both_ways(_pair(C, H, W, K, False), batch, pct, 1, bias=False)
+
+
+@pytest.mark.parametrize("relu", [True, False])
+@pytest.mark.parametrize("case", EDGES, ids=lambda c: "x".join(map(str, c)))
+def test_infinities_and_nan(case, relu):
+    # in the corners and the middle of some images; those between them have to stay finite
+    C, H, W, K, batch, pct = case
+    model = _pair(C, H, W, K, relu)
+    x = workloads.batch_input(model, batch, 5)
+    x[0, 1, 0, 0] = float("inf")
+    x[1, C - 1, H - 1, W - 1] = -float("inf")
+    x[2, 0, H // 2, W // 2] = float("nan")
+    x[3] = -3.3895e38
+    for t in _both_ways(model, batch, pct, 1, x=x):
+        assert t[4:].isfinite().all()
+        assert t[:3].isfinite().float().mean() > 0.5   # pixels whose window does not touch them
 
 
 @pytest.mark.parametrize("case", SEPARATE, ids=lambda c: "x".join(map(str, c)))
@@ -87,6 +118,7 @@ def test_whole_model_with_and_without_shared_launches(reuse):
         for fused in (False, True):
             gpulet.set_conv_pool_fusion(fused)
             try:
+                dm.workspace(3)[0].fill_(255)   # what a launch leaves out stays NaN
                 before = p.kernel_launches()
                 y, _ = dm.run(p, xd)
                 n = p.kernel_launches() - before
