@@ -301,9 +301,14 @@ gpulet_status gpulet_conv3x3_maxpool2_fwd(const void *x, const void *w, const fl
  * epilogue, costs the layer at most 15 % more than the kernel it would run
  * otherwise; the layer's own output buffer is then left unwritten.  The same
  * switch governs runs of small layers (convolutions, max pools, fully connected
- * layers whose tensors of one image fit in LDS together, as LeNet-5's), which go
- * out as one launch that still writes every tensor.  Results are
- * bit-identical either way.  Process-wide.
+ * layers whose tensors of one image fit in LDS together, as LeNet-5's) and
+ * depthwise 3x3 / stride 1 convolutions with the 1x1 convolution behind them,
+ * which go out as one launch where that is estimated to be faster.  Such a
+ * launch writes every tensor that a later layer reads, and leaves out those whose
+ * buffer a later layer of the run takes over, or overwrites before anybody else has
+ * read it.  While a tile is forced (gpulet_set_conv_tile) or a layer may split
+ * its depth (gpulet_set_conv_split_k) the layers concerned keep launches of
+ * their own.  Results are bit-identical either way.  Process-wide.
  */
 gpulet_status gpulet_set_conv_pool_fusion(int on);
 

@@ -10,10 +10,11 @@
 // Bound: the chain of barriers and latencies of one image; matrix cores and LDS are mostly idle.  16
 // wavefronts, because only other wavefronts hide those latencies.  Weights of fully connected layers come
 // to LDS by transfers while earlier layers run: fetched as matrix fragments, 64 bytes of a row at a time,
-// they kept the load path busy for 2.7 us per layer.  LeNet-5 at batch 32 on 256 CUs: seven launches 29.3 us
-// a pass, one launch 15.3 (of them 1.2 until the arguments are there, 2 until the image and the filters are,
-// 3.1 and 1.2 the convolutions, 1 and 0.6 the pools, 1.3 each fully connected layer).  It is the faster way
-// at every batch size: 512 images 75 and 36 us, 2048 images 195 and 112; on 64 CUs 2048 images 648 and 413.
+// they kept the load path busy for 2.7 us per layer.  LeNet-5 on 256 CUs, seven launches and one: 1 image 24.1
+// and 12.4 us a pass, 32 images 29.2 and 12.8, 512 images 68 and 24, 2048 images 187 and 90; on 64 CUs 2048 images
+// 642 and 349.  (Stamps at 15.3 us, when 101 spilled scalar registers still cost the convolutions 2.5: 1.2 until the
+// arguments are there, 2 until the image and the filters are, 3.1 and 1.2 the convolutions, 1 and 0.6 the pools, 1.3
+// each fully connected layer.)
 //
 // Every layer adds its products in the order of the kernel that runs it alone (convolution: depth
 // as stored, or 64-channel blocks with the taps inside where that kernel walks so; fully connected:
@@ -547,7 +548,7 @@ double separate_us(const ChainLayer *l, int n, int N, int n_cu) {
 
 // A workgroup takes its image through the run alone, on one CU: few and small layers win by the launches they
 // save, and by what separate kernels of many images waste on 8 channels; wide layers, short runs and several images per
-// CU lose (LeNet-5 wins at every batch, batch 2048 186 and 96 us; 1x1 256 -> 64 -> 256 on 7x7 at batch 1 7.3 and 13.7,
+// CU lose (LeNet-5 wins at every batch, batch 2048 187 and 90 us; 1x1 256 -> 64 -> 256 on 7x7 at batch 1 7.3 and 13.7,
 // at batch 2048 30 and 102; 256 -> 256 -> 32 features at batch 2048 10.6 and 60).  Of the runs above 991 fit as a whole:
 // with this line 565 share a launch, a third faster in the mean (17 of them 3 % slower and more), 0.7 % above always
 // taking the faster way; sharing all of them is 10 % slower than sharing none.
